@@ -374,22 +374,29 @@ size_t frame_workspace_bytes(const lnm_net_s* net, const lnm_volume* vol, const 
 hipError_t static_scratch_address(void** out);
 
 // ---------------------------------------------------------------- training kernels (train.hip)
-// Layer geometry shared by the backward kernels.
+// Weight gradient of one layer (launch_wgrad3x3 fills in the tiling).
 struct WgradArgs {
   ConvArgs x;       // the layer's (virtual) input, as the forward gather sees it
   const float* e;   // [B][H][W][co] gradient at the pre-activation
   int co, ci;       // real channels
-  int ci_pad16;     // ci rounded up to 16
-  int tiles_per_group;
-  float* partial;   // [groups * 4][co_pad][ci_pad16][9]
+  int co_pad, ci_pad, tiles_per_group;
+  float* partial;       // [groups][co_pad][9][ci_pad]
+  float* bias_partial;  // [groups][co_pad]
+  float* grad_w;        // [co][ci][9]
+  float* grad_b;        // [co]
 };
+// Channel blocks of 16 per workgroup (wm output x wn input), channels rounded
+// up to them, and the pixel tiles of each workgroup (plan.hip).
+struct WgradTiling {
+  int wm, wn, co_pad, ci_pad, groups, tiles_per_group;
+};
+WgradTiling wgrad_tiling(int co, int ci, int B, int h, int w);
+// weight and bias gradients (the sums and their reduction)
 hipError_t launch_wgrad3x3(int mode, const WgradArgs& a, int* n_partials, hipStream_t s);
-hipError_t launch_wgrad_reduce(const float* partial, int n_partials, int co, int ci, int co_pad, int ci_pad16,
-                               float* grad_w, hipStream_t s);
 hipError_t launch_loss(const float* y, const float* t, float* dz, float* partial, long n, float* loss,
                        hipStream_t s);
-hipError_t launch_colsum(const float* e, long P, int C, float* partial, float* out, hipStream_t s);
 hipError_t launch_relu_mask(float* g, const float* y, long n, hipStream_t s);
+// partial: kHeadBwdBlocks (6 C + 6) floats
 hipError_t launch_head_bwd(const float* dz, const float* w, const float* x, long P, int C, float* e_out,
                            float* grad_w, float* grad_b, float* partial, hipStream_t s);
 hipError_t launch_route_concat(const float* dx, int B, int H, int W, int c0, int c1, float* g_skip, float* g_low,
@@ -402,7 +409,7 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, long n, flo
 hipError_t launch_pack_f32(const float* flat_w, const float* flat_b, const LayerDesc& d, int dgrad, char* dst,
                            size_t w_off, size_t b_off, hipStream_t s);
 constexpr int kLossBlocks = 256;
-constexpr int kColsumBlocks = 128;
+constexpr int kHeadBwdBlocks = 512;
 }  // namespace lnm
 
 struct lnm_trainer_s {

@@ -93,12 +93,9 @@ struct AdapterTrainPlan {
 
 struct TrainPlan {
   Plan fwd;
-  size_t g_base, lm, dz, dx, part, colpart, losspart, loss, bytes;
-  std::vector<int> tiles_per_group;
+  size_t g_base, lm, dz, dx, part, bpart, headpart, losspart, loss, bytes;
   AdapterTrainPlan ad;
 };
-
-constexpr size_t kPartialBudget = 48u << 20;  // bytes of weight-gradient partial sums per layer
 
 TrainPlan train_plan(const lnm_net_s* net, int B, int H, int W, int ad_c = 0) {
   TrainPlan t;
@@ -115,25 +112,19 @@ TrainPlan train_plan(const lnm_net_s* net, int B, int H, int W, int ad_c = 0) {
   const size_t P = (size_t)B * H * W;
   t.lm = take(sizeof(float) * P * 6);
   t.dz = take(sizeof(float) * P * 6);
-  size_t dx = 0, part = 0;
-  int maxc = 6;
+  size_t dx = 0, part = 0, bpart = 0;
   for (size_t i = 0; i < sch.size(); ++i) {
     const LayerDesc& d = net->layers[i];
     const int h = H >> sch[i].level, w = W >> sch[i].level;
     if (sch[i].mode == G_POOL || sch[i].mode == G_CONCAT_UP) dx = std::max(dx, (size_t)B * h * w * d.ci);
-    const int tiles = B * ((w + 15) / 16) * ((h + 7) / 8);
-    const int co_pad = (d.co + kBN - 1) / kBN * kBN, ci16 = (d.ci + 15) / 16 * 16;
-    const size_t per_group = sizeof(float) * 4 * (size_t)co_pad * ci16 * 9;
-    int groups = (int)std::max<size_t>(1, std::min<size_t>({(size_t)tiles, kPartialBudget / per_group, 512}));
-    const int tpg = (tiles + groups - 1) / groups;
-    groups = (tiles + tpg - 1) / tpg;
-    t.tiles_per_group.push_back(tpg);
-    part = std::max(part, per_group * groups);
-    maxc = std::max(maxc, d.co);
+    const WgradTiling wt = wgrad_tiling(d.co, d.ci, B, h, w);
+    part = std::max(part, (size_t)wt.groups * wt.co_pad * 9 * wt.ci_pad);
+    bpart = std::max(bpart, (size_t)wt.groups * wt.co_pad);
   }
   t.dx = take(sizeof(float) * std::max<size_t>(dx, 1));
-  t.part = take(part);
-  t.colpart = take(sizeof(float) * kColsumBlocks * maxc);
+  t.part = take(sizeof(float) * part);
+  t.bpart = take(sizeof(float) * bpart);
+  t.headpart = take(sizeof(float) * kHeadBwdBlocks * (6 * (size_t)net->layers.back().ci + 6));
   t.losspart = take(sizeof(float) * kLossBlocks);
   t.loss = take(sizeof(float));
   t.ad = AdapterTrainPlan{};
@@ -201,7 +192,7 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
   auto G = [&](int i) { return reinterpret_cast<float*>(ws + tp.g_base + tp.fwd.out_off[i]); };
   float* dx = reinterpret_cast<float*>(ws + tp.dx);
   float* part = reinterpret_cast<float*>(ws + tp.part);
-  float* colpart = reinterpret_cast<float*>(ws + tp.colpart);
+  float* bpart = reinterpret_cast<float*>(ws + tp.bpart);
 
   const int nl = (int)net->layers.size(), hi = nl - 1, last = nl - 2;
   const LayerDesc& hd = net->layers[hi];
@@ -259,7 +250,8 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
     LNM_HIP_CHECK(launch_loss(lm, target, dz, reinterpret_cast<float*>(ws + tp.losspart), (long)P * 6,
                               reinterpret_cast<float*>(ws + tp.loss), s));
     LNM_HIP_CHECK(launch_head_bwd(dz, reinterpret_cast<const float*>(net->dev + hd.w_off), Y(last), (long)P,
-                                  hd.ci, G(last), tr->g + tr->flat_w[hi], tr->g + tr->flat_b[hi], nullptr, s));
+                                  hd.ci, G(last), tr->g + tr->flat_w[hi], tr->g + tr->flat_b[hi],
+                                  reinterpret_cast<float*>(ws + tp.headpart), s));
   }
   for (int i = last; i >= 0; --i) {
     const LayerDesc& d = net->layers[i];
@@ -267,7 +259,6 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
     const int h = H >> c.level, w = W >> c.level;
     const long n_out = (long)B * h * w * d.co;
     if (i != last) LNM_HIP_CHECK(launch_relu_mask(G(i), Y(i), n_out, s));  // dL/d(pre-activation)
-    LNM_HIP_CHECK(launch_colsum(G(i), (long)B * h * w, d.co, colpart, tr->g + tr->flat_b[i], s));
     // the layer's input exactly as the forward gather read it
     ConvArgs x{};
     x.src0 = c.src0 < 0 ? static_cast<const void*>(guide) : Y(c.src0);
@@ -282,16 +273,15 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
     wa.e = G(i);
     wa.co = d.co;
     wa.ci = d.ci;
-    wa.ci_pad16 = (d.ci + 15) / 16 * 16;
-    wa.tiles_per_group = tp.tiles_per_group[i];
     wa.partial = part;
+    wa.bias_partial = bpart;
+    wa.grad_w = tr->g + tr->flat_w[i];
+    wa.grad_b = tr->g + tr->flat_b[i];
     int n_part = 0;
     {
       ProfScope ps(ctx, LNM_K_CONV, s);
       LNM_HIP_CHECK(launch_wgrad3x3(c.mode, wa, &n_part, s));
     }
-    LNM_HIP_CHECK(launch_wgrad_reduce(part, n_part, d.co, d.ci, (d.co + kBN - 1) / kBN * kBN, wa.ci_pad16,
-                                      tr->g + tr->flat_w[i], s));
     if (i == 0) break;
     // gradient with respect to the layer's input: the convolution with the
     // transposed, tap-mirrored weights
