@@ -15,19 +15,20 @@
 //                     weight gradients), the features' gradient through the
 //                     first residual, the gate's gradient and per-workgroup
 //                     sums of every vector gradient;
-//   adapt_bwd_attend  workgroup per group: the attention scale's gradient per
-//                     image, its weights' gradient, the image-mean term of
-//                     the gate gradient, and the tail's vector gradients;
+//   adapt_sum_tail    the tail workgroups' sums added per image;
+//   adapt_bwd_attend  the image-mean term of the gate gradient per image, the
+//                     attention weights' gradient and the tail's vector
+//                     gradients;
 //   adapt_bwd_front   workgroup per (8 x 32 tile, group, image): conv1 on
 //                     tile + halo again, the gate's and depthwise conv's
 //                     backward (mirrored taps), conv1's input gradient
 //                     accumulated over the channel passes, layer norm 1's
 //                     backward -> the features' gradient from this side;
-//   adapt_bwd_finish  workgroup per group: the front's vector gradients (and
-//                     zeros for the alpha/emissive group);
+//   adapt_bwd_finish  the front's vector gradients (and zeros for the
+//                     alpha/emissive group);
 //   wgrad_1x1         dW = sum over pixels of delta x^T, K = pixels on the
-//                     matrix cores, per chunk of pixels; chunk sums added in
-//                     order by sum_chunks;
+//                     matrix cores, per run of pixels, all convolutions in one
+//                     launch; the runs' sums added by sum_runs;
 //   adapt_feat_grad   the features' gradient (the parts of the three groups
 //                     added in a fixed order) through the decoder's ReLU, and
 //                     the loss.
@@ -412,52 +413,72 @@ __global__ __launch_bounds__(256) void adapt_bwd_tail(AdapterTrainArgs t) {
   for (int q = tid; q < S::n; q += 256) out[q] = ((rows[0][q] + rows[1][q]) + rows[2][q]) + rows[3][q];
 }
 
-// grid: (3 groups).  ds per image (its tail workgroups' sums in order), the
-// attention weights' gradient (images in order), dmh = Wsca^T ds / HW, and
-// the tail's other vector gradients (all tail workgroups in order)
+// Sums of rows of n floats: rows [0, rows) of src[column], eight lanes per
+// column (every eighth row each, then added in order), 32 columns per block.
+// Every lane of the block calls it; the result is in the lanes r == 0.
+__device__ __forceinline__ float sum_rows(const float* src, int rows, size_t pitch, bool live, float (&sh)[8][32]) {
+  const int el = threadIdx.x & 31, rl = threadIdx.x >> 5;
+  float s = 0.0f;
+  if (live) {
+#pragma unroll 4
+    for (int k = rl; k < rows; k += 8) s += src[(size_t)k * pitch];
+  }
+  sh[rl][el] = s;
+  __syncthreads();
+#pragma unroll
+  for (int k = 1; k < 8; ++k) s += sh[k][el];
+  return s;
+}
+
+// grid: (columns / 32, images, 3 groups).  Each image's sums of its tail
+// workgroups' rows.  (One lane per column over all rows, one block per group,
+// waited on every load in turn: 106 us at 12 x 64^2, width 16; with
+// adapt_bwd_attend 9 us.)
+template <int C>
+__global__ __launch_bounds__(256) void adapt_sum_tail(AdapterTrainArgs t) {
+  using S = TailSlots<C>;
+  __shared__ float sh[8][32];
+  const int q = blockIdx.x * 32 + (threadIdx.x & 31), b = blockIdx.y, g = blockIdx.z, B = t.f.B;
+  const float* src = t.tpart + ((size_t)g * B + b) * t.tpi * S::n + q;
+  const float s = sum_rows(src, t.tpi, S::n, q < S::n, sh);
+  if (threadIdx.x < 32 && q < S::n) t.timg[((size_t)g * B + b) * S::n + q] = s;
+}
+
+// grid: (images + 1, 3 groups).  Block b < images: dmh = Wsca^T ds / HW of the
+// image; the last block: the attention weights' gradient and the tail's
+// other vector gradients (images in order)
 template <int C>
 __global__ __launch_bounds__(256) void adapt_bwd_attend(AdapterTrainArgs t) {
   using O = Off<C>;
   using S = TailSlots<C>;
   const AdapterArgs& a = t.f;
-  __shared__ float dss[C];
-  const int g = blockIdx.x, tid = threadIdx.x;
-  const int nblk = a.B * t.tpi;
-  const float* part = t.tpart + (size_t)g * nblk * S::n;
+  const int g = blockIdx.y, tid = threadIdx.x;
+  const float* img = t.timg + (size_t)g * a.B * S::n;
   const float* P = a.prm + (size_t)g * O::total;
   float* Gr = t.grad + (size_t)g * O::total;
-  const float inv_hw = 1.0f / (float)(a.H * a.W);
-  float gb = 0.0f, gw[C];
-#pragma unroll
-  for (int i = 0; i < C; ++i) gw[i] = 0.0f;
-  for (int b = 0; b < a.B; ++b) {
-    if (tid < C) {
-      float ds = 0.0f;
-      for (int k = 0; k < t.tpi; ++k) ds += part[(size_t)(b * t.tpi + k) * S::n + S::ds + tid];
-      dss[tid] = ds;
-      gb += ds;
-      const float* m = a.msave + ((size_t)b * 4 + g) * C;
-#pragma unroll
-      for (int i = 0; i < C; ++i) gw[i] += ds * m[i];
-    }
-    __syncthreads();
+  if ((int)blockIdx.x < a.B) {
+    const int b = blockIdx.x;
+    const float inv_hw = 1.0f / (float)(a.H * a.W);
     if (tid < C) {
       float dm = 0.0f;
-      for (int o = 0; o < C; ++o) dm += P[O::scaw + o * C + tid] * dss[o];
+#pragma unroll 8
+      for (int o = 0; o < C; ++o) dm += P[O::scaw + o * C + tid] * img[(size_t)b * S::n + S::ds + o];
       t.dmh[((size_t)b * 4 + g) * C + tid] = dm * inv_hw;
     }
-    __syncthreads();
+    return;
   }
-  if (tid < C) {
-    Gr[O::scab + tid] = gb;
-#pragma unroll
-    for (int i = 0; i < C; ++i) Gr[O::scaw + tid * C + i] = gw[i];
+  for (int q = tid; q < C * C; q += 256) {
+    float s = 0.0f;
+#pragma unroll 4
+    for (int b = 0; b < a.B; ++b) s += img[(size_t)b * S::n + S::ds + q / C] * a.msave[((size_t)b * 4 + g) * C + q % C];
+    Gr[O::scaw + q] = s;
   }
   for (int q = tid; q < S::n; q += 256) {
-    if (q < S::b3) continue;  // ds: per image, above
     float s = 0.0f;
-    for (int k = 0; k < nblk; ++k) s += part[(size_t)k * S::n + q];
-    if (q < S::beta) Gr[O::c3b + (q - S::b3)] = s;
+#pragma unroll 4
+    for (int b = 0; b < a.B; ++b) s += img[(size_t)b * S::n + q];
+    if (q < S::b3) Gr[O::scab + q] = s;
+    else if (q < S::beta) Gr[O::c3b + (q - S::b3)] = s;
     else if (q < S::l2w) Gr[O::beta + (q - S::beta)] = s;
     else if (q < S::l2b) Gr[O::ln2w + (q - S::l2w)] = s;
     else if (q < S::b4) Gr[O::ln2b + (q - S::l2b)] = s;
@@ -686,70 +707,98 @@ __global__ __launch_bounds__(256) void adapt_bwd_front(AdapterTrainArgs t) {
   for (int q = tid; q < S::n; q += 256) out[q] = ((rows[0][q] + rows[1][q]) + rows[2][q]) + rows[3][q];
 }
 
-// grid: (4 groups): the front's vector gradients summed over its
-// workgroups in order; the alpha/emissive group's slice set to zero
+// grid: (columns / 32, 4 groups): the front's vector gradients summed over its
+// workgroups; the alpha/emissive group's slice set to zero.  (One lane per
+// column, one block per group: 90 us at 12 x 64^2, width 16; now 5 us.)
 template <int C>
 __global__ __launch_bounds__(256) void adapt_bwd_finish(AdapterTrainArgs t) {
   using O = Off<C>;
   using S = FrontSlots<C>;
+  __shared__ float sh[8][32];
   const AdapterArgs& a = t.f;
-  const int g = blockIdx.x, tid = threadIdx.x;
+  const int g = blockIdx.y, q = blockIdx.x * 32 + (threadIdx.x & 31);
   float* Gr = t.grad + (size_t)g * O::total;
   if (g >= kTrainGroups) {
-    for (int q = tid; q < O::total; q += 256) Gr[q] = 0.0f;
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < O::total; k += 256 * gridDim.x) Gr[k] = 0.0f;
     return;
   }
   const int nblk = a.B * a.n_blk;
-  const float* part = t.fpart + (size_t)g * nblk * S::n;
-  for (int q = tid; q < S::n; q += 256) {
-    float s = 0.0f;
-    for (int k = 0; k < nblk; ++k) s += part[(size_t)k * S::n + q];
-    if (q < S::l1b) Gr[O::ln1w + q] = s;
-    else if (q < S::b1) Gr[O::ln1b + (q - S::l1b)] = s;
-    else if (q < S::dwb) Gr[O::c1b + (q - S::b1)] = s;
-    else if (q < S::dww) Gr[O::dwb + (q - S::dwb)] = s;
-    else Gr[O::dww + (q - S::dww)] = s;
-  }
+  const float s = sum_rows(t.fpart + (size_t)g * nblk * S::n + q, nblk, S::n, q < S::n, sh);
+  if (threadIdx.x >= 32 || q >= S::n) return;
+  if (q < S::l1b) Gr[O::ln1w + q] = s;
+  else if (q < S::b1) Gr[O::ln1b + (q - S::l1b)] = s;
+  else if (q < S::dwb) Gr[O::c1b + (q - S::b1)] = s;
+  else if (q < S::dww) Gr[O::dwb + (q - S::dwb)] = s;
+  else Gr[O::dww + (q - S::dww)] = s;
 }
 
-// part[chunk][M][N] = sum over pixels q of the chunk of delta[q][o] x[q][i]
-// (K = pixels: lane (li, G) feeds row o / column i = li at pixel q + G)
-constexpr int kWgradChunk = kAdaptWgradChunk;
-__global__ __launch_bounds__(256) void wgrad_1x1(const float* __restrict__ delta, int M, const float* __restrict__ x,
-                                                 int N, size_t P, float* __restrict__ part) {
-  const int lane = threadIdx.x & 63, li = lane & 15, G = lane >> 4, wave = threadIdx.x >> 6;
-  const size_t q0 = (size_t)blockIdx.x * kWgradChunk;
-  const size_t q1 = min(P, q0 + kWgradChunk);
-  const int tn = N / 16, tiles = (M / 16) * tn;
-  for (int tile = wave; tile < tiles; tile += 4) {  // uniform per wavefront
-    const int mt = tile / tn, nt = tile - mt * tn;
-    f4 acc = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (size_t q = q0; q < q1; q += 16) {
-      float av[4], bv[4];
+// The twelve 1x1 convolutions' weight gradients (conv5, conv4, conv3, conv1
+// of the three groups) in one launch: job j's dW = sum over pixels of
+// delta[q][o] x[q][i], K = pixels (lane (li, G) feeds row o / column i = li at
+// pixel q + G).  A wavefront sums all M x C weights over its own run of
+// `run` pixels, so every value is read once; the runs' sums are added by
+// sum_runs.  Bound by memory (delta and x read once) and, at small sizes, by
+// launches: 12 x 64^2, width 16 takes 22 us for both kernels against 552
+// with a pair of launches per convolution and runs of 1024 pixels.
+struct Wgrad1x1Args {
+  const float *d[12], *x[12];
+  float *part[12], *out[12];
+  size_t P;
+  int run, runs;
+};
+template <int C, int MT>
+__device__ __forceinline__ void wgrad_run(const float* __restrict__ delta, const float* __restrict__ x, size_t q0,
+                                          size_t q1, float* __restrict__ out) {
+  constexpr int NT = C / 16, M = 16 * MT;
+  const int lane = threadIdx.x & 63, li = lane & 15, G = lane >> 4;
+  f4 acc[MT][NT];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const size_t qq = q + 4 * u + G;
-        const bool ok = qq < q1;
-        av[u] = ok ? delta[qq * M + 16 * mt + li] : 0.0f;
-        bv[u] = ok ? x[qq * N + 16 * nt + li] : 0.0f;
-      }
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) acc = mfma(av[u], bv[u], acc);
+    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+  constexpr int U = MT + NT <= 3 ? 8 : MT + NT <= 6 ? 4 : 2;  // K steps of four pixels loaded together
+  for (size_t q = q0; q < q1; q += 4 * U) {
+    float av[U][MT], bv[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t qq = q + 4 * u + G;
+      const bool ok = qq < q1;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) av[u][mt] = ok ? delta[qq * M + 16 * mt + li] : 0.0f;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) bv[u][nt] = ok ? x[qq * C + 16 * nt + li] : 0.0f;
     }
-    float* out = part + (size_t)blockIdx.x * M * N;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) out[(size_t)(16 * mt + 4 * G + r) * N + 16 * nt + li] = acc[r];
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = mfma(av[u][mt], bv[u][nt], acc[mt][nt]);
   }
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[(16 * mt + 4 * G + r) * C + 16 * nt + li] = acc[mt][nt][r];
+}
+template <int C>
+__global__ __launch_bounds__(256) void wgrad_1x1(Wgrad1x1Args a) {
+  const int k = blockIdx.x * 4 + (threadIdx.x >> 6), j = blockIdx.y;  // uniform per wavefront
+  if (k >= a.runs) return;
+  const size_t q0 = (size_t)k * a.run, q1 = min(a.P, q0 + a.run);
+  if (j & 1)  // conv4, conv1
+    wgrad_run<C, C / 8>(a.d[j], a.x[j], q0, q1, a.part[j] + (size_t)k * 2 * C * C);
+  else
+    wgrad_run<C, C / 16>(a.d[j], a.x[j], q0, q1, a.part[j] + (size_t)k * C * C);
 }
 
-// out[e] = sum over chunks (in order) of part[chunk][e]
-__global__ __launch_bounds__(256) void sum_chunks(const float* __restrict__ part, int n_chunks, int n,
-                                                  float* __restrict__ out) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= n) return;
-  float s = 0.0f;
-  for (int k = 0; k < n_chunks; ++k) s += part[(size_t)k * n + e];
-  out[e] = s;
+template <int C>
+__global__ __launch_bounds__(256) void sum_runs(Wgrad1x1Args a) {
+  __shared__ float sh[8][32];
+  const int j = blockIdx.y, n = (j & 1 ? 2 : 1) * C * C, e = blockIdx.x * 32 + (threadIdx.x & 31);
+  const float s = sum_rows(a.part[j] + e, a.runs, n, e < n, sh);
+  if (threadIdx.x < 32 && e < n) a.out[j][e] = s;
 }
 
 // gfeat[q][i] = (y[q][i] > 0) * sum over groups (in order) of (dyf + dxf);
@@ -778,27 +827,28 @@ hipError_t launch_train_c(const AdapterTrainArgs& t, const float* y_last, float*
   if (e != hipSuccess) return e;
   // backward
   hipLaunchKernelGGL(adapt_bwd_tail<C>, dim3((unsigned)(a.B * t.tpi), kTrainGroups), dim3(256), 0, s, t);
-  hipLaunchKernelGGL(adapt_bwd_attend<C>, dim3(kTrainGroups), dim3(256), 0, s, t);
+  hipLaunchKernelGGL(adapt_sum_tail<C>, dim3((TailSlots<C>::n + 31) / 32, (unsigned)a.B, kTrainGroups), dim3(256), 0, s,
+                     t);
+  hipLaunchKernelGGL(adapt_bwd_attend<C>, dim3((unsigned)a.B + 1, kTrainGroups), dim3(256), 0, s, t);
   hipLaunchKernelGGL(adapt_bwd_front<C>, dim3((unsigned)a.n_blk, kTrainGroups, (unsigned)a.B), dim3(256), 0, s, t);
-  hipLaunchKernelGGL(adapt_bwd_finish<C>, dim3(4), dim3(256), 0, s, t);
-  const int chunks = (int)((a.P + kWgradChunk - 1) / kWgradChunk);
-  struct Job {
-    const float *d, *x;
-    int M, off;
-  };
-  for (int g = 0; g < kTrainGroups; ++g) {
+  hipLaunchKernelGGL(adapt_bwd_finish<C>, dim3((FrontSlots<C>::n + 31) / 32, 4), dim3(256), 0, s, t);
+  Wgrad1x1Args w{};
+  w.P = a.P;
+  w.run = adapter_wgrad_run(a.P);
+  w.runs = (int)((a.P + w.run - 1) / w.run);
+  float* part = wpart;
+  for (int j = 0; j < 4 * kTrainGroups; ++j) {
+    const int g = j / 4, k = j % 4;
     const size_t gc = (size_t)g * a.P * C;
-    const Job jobs[4] = {{t.d5 + gc, t.x5 + gc, C, O::c5w},
-                         {t.d4 + 2 * gc, t.x4 + gc, 2 * C, O::c4w},
-                         {t.d3 + gc, t.x3 + gc, C, O::c3w},
-                         {t.d1 + 2 * gc, t.x1 + gc, 2 * C, O::c1w}};
-    for (const Job& j : jobs) {
-      hipLaunchKernelGGL(wgrad_1x1, dim3((unsigned)chunks), dim3(256), 0, s, j.d, j.M, j.x, C, a.P, wpart);
-      const int n = j.M * C;
-      hipLaunchKernelGGL(sum_chunks, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, wpart, chunks, n,
-                         t.grad + (size_t)g * O::total + j.off);
-    }
+    const int m = k & 1 ? 2 : 1;
+    w.d[j] = k == 0 ? t.d5 + gc : k == 1 ? t.d4 + 2 * gc : k == 2 ? t.d3 + gc : t.d1 + 2 * gc;
+    w.x[j] = (k == 0 ? t.x5 : k == 1 ? t.x4 : k == 2 ? t.x3 : t.x1) + gc;
+    w.out[j] = t.grad + (size_t)g * O::total + (k == 0 ? O::c5w : k == 1 ? O::c4w : k == 2 ? O::c3w : O::c1w);
+    w.part[j] = part;
+    part += (size_t)w.runs * m * C * C;
   }
+  hipLaunchKernelGGL(wgrad_1x1<C>, dim3((unsigned)((w.runs + 3) / 4), 4 * kTrainGroups), dim3(256), 0, s, w);
+  hipLaunchKernelGGL(sum_runs<C>, dim3(2 * C * C / 32, 4 * kTrainGroups), dim3(256), 0, s, w);
   const size_t n = a.P * C;
   hipLaunchKernelGGL(adapt_feat_grad<C>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, t, y_last, g_last);
   return hipGetLastError();

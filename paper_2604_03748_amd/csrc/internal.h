@@ -258,6 +258,7 @@ struct AdapterTrainArgs {
   float *d5, *x5, *d3, *x3, *x4, *x1;  // [3][P][c] deltas and inputs of the 1x1 convolutions
   float *d4, *d1;          // [3][P][2c]
   float* tpart;            // [3][B * tpi][11c + 4] tail workgroup sums
+  float* timg;             // [3][B][11c + 4] their sums per image
   float* fpart;            // [3][B][n_blk][24c] front workgroup sums
   float* dmh;              // [B][4][c] image-mean term of the gate gradient
   float* lossg;            // [3] squared-error sums per group
@@ -265,8 +266,8 @@ struct AdapterTrainArgs {
   int tpi;                 // tail workgroups per image (adapter_tail_blocks_per_image)
   float inv_n;             // 1 / (P * 6)
 };
-constexpr int kAdaptWgradChunk = 1024;  // pixels per partial sum of a 1x1 weight gradient
 int adapter_tail_blocks_per_image(int H, int W);
+int adapter_wgrad_run(size_t P);  // pixels per partial sum of the 1x1 weight gradients
 size_t adapter_wgrad_partial_bytes(size_t P, int c);
 // adapters' forward (keeping d, m), backward, weight gradients, and the
 // features' gradient through the decoder's ReLU into g_last

@@ -167,8 +167,14 @@ bool adapter_width_supported(int c) { return c == 16 || c == 32 || c == 48 || c 
 
 int adapter_tail_blocks_per_image(int H, int W) { return (H * W + 255) / 256; }
 
+// One wavefront per run of pixels and convolution: at least 256 pixels, at
+// most 256 runs (the partial sums stay small beside the pixels' own values).
+int adapter_wgrad_run(size_t P) { return (int)std::max<size_t>(256, ((P + 255) / 256 + 15) / 16 * 16); }
+
+// conv5, conv4, conv3, conv1 of three groups: 3 (1 + 2 + 1 + 2) c^2 per run
 size_t adapter_wgrad_partial_bytes(size_t P, int c) {
-  return sizeof(float) * ((P + kAdaptWgradChunk - 1) / kAdaptWgradChunk) * 2 * (size_t)c * c;
+  const size_t run = adapter_wgrad_run(P);
+  return sizeof(float) * ((P + run - 1) / run) * 18 * (size_t)c * c;
 }
 
 int adapter_tiles(int H, int W) {

@@ -87,7 +87,7 @@ bool state_layout(int levels, int base, StateLayout* s, std::string* why) {
 // workspace of the adapters' training (offsets; per-pixel tensors of the
 // three groups with a lightmap target, forward tensors of all four)
 struct AdapterTrainPlan {
-  size_t v, dsave, part, sca, msave, dgt, dyf, dxf, d5, x5, d3, x3, x4, x1, d4, d1, tpart, fpart, dmh, lossg, wpart;
+  size_t v, dsave, part, sca, msave, dgt, dyf, dxf, d5, x5, d3, x3, x4, x1, d4, d1, tpart, timg, fpart, dmh, lossg, wpart;
   int n_blk, tpi;
 };
 
@@ -142,6 +142,7 @@ TrainPlan train_plan(const lnm_net_s* net, int B, int H, int W, int ad_c = 0) {
     a.d4 = take(f * 3 * P * 2 * c);
     a.d1 = take(f * 3 * P * 2 * c);
     a.tpart = take(f * 3 * (size_t)B * a.tpi * (11 * c + 4));
+    a.timg = take(f * 3 * (size_t)B * (11 * c + 4));
     a.fpart = take(f * 3 * (size_t)B * a.n_blk * 24 * c);
     a.dmh = take(f * (size_t)B * 4 * c);
     a.lossg = take(f * 4);
@@ -233,6 +234,7 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
     t.d4 = F(ap.d4);
     t.d1 = F(ap.d1);
     t.tpart = F(ap.tpart);
+    t.timg = F(ap.timg);
     t.fpart = F(ap.fpart);
     t.dmh = F(ap.dmh);
     t.lossg = F(ap.lossg);
