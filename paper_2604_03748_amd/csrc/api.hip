@@ -352,7 +352,7 @@ Plan plan_workspace(const lnm_net_s* net, int B, int H, int W) {
 
 lnm_status run_unet(lnm_ctx_s* ctx, const lnm_net_s* net, int B, int H, int W, const float* guide, float* lm,
                     float* logits, char* ws, hipStream_t s, const CompositeArgs* comp, bool fuse_head,
-                    bool fuse_first) {
+                    bool fuse_first, bool split) {
   const Plan p = plan_workspace(net, B, H, W);
   const int L = net->levels;
   auto buf = [&](int i) { return static_cast<void*>(ws + p.out_off[i]); };
@@ -376,6 +376,7 @@ lnm_status run_unet(lnm_ctx_s* ctx, const lnm_net_s* net, int B, int H, int W, c
     a.bias = reinterpret_cast<const float*>(net->dev + d.b_off);
     a.out = buf(li);
     a.relu = 1;
+    a.split = split;
     if (d.prec == LNM_FP8_E4M3) {
       a.in_scale = src >= 0 ? net->act_scale[src] : 1.0f;
       a.w_scale = d.s_off ? reinterpret_cast<const float*>(net->dev + d.s_off) : nullptr;
@@ -547,7 +548,7 @@ lnm_status frame_impl(lnm_ctx_s* ctx, const lnm_net_s* net, const lnm_volume* vo
   a.rgba = rgba;
   a.P = c.H * c.W;
   return run_unet(ctx, net, 1, c.H, c.W, guide, lightmaps, nullptr, static_cast<char*>(workspace), s,
-                  rgba ? &a : nullptr, true, true);
+                  rgba ? &a : nullptr, true, true, true);
 }
 
 size_t frame_workspace_bytes(const lnm_net_s* net, const lnm_volume* vol, const lnm_camera* cam,
@@ -855,7 +856,7 @@ lnm_status lnm_infer(lnm_ctx ctx, lnm_net net, int32_t batch, int32_t H, int32_t
   lnm_status st = check_infer(net, batch, H, W, ws_bytes, workspace);
   if (st) return st;
   return run_unet(ctx, net, batch, H, W, guide, lightmaps, logits, static_cast<char*>(workspace),
-                  (hipStream_t)stream, nullptr, true, true);
+                  (hipStream_t)stream, nullptr, true, true, true);
 }
 
 lnm_status lnm_composite(lnm_ctx ctx, const lnm_camera* cam, const lnm_light* lights, int32_t n_lights,
@@ -984,7 +985,7 @@ lnm_status lnm_infer_adapters(lnm_ctx ctx, lnm_adapters ad, int32_t batch, int32
   if (ws_bytes < ap.bytes) return fail(LNM_ERR_SHAPE, "workspace too small: need " + std::to_string(ap.bytes));
   char* ws = static_cast<char*>(workspace);
   hipStream_t s = (hipStream_t)stream;
-  st = run_unet(ctx, ad->net, batch, H, W, guide, nullptr, nullptr, ws, s, nullptr, false, true);  // trunk only
+  st = run_unet(ctx, ad->net, batch, H, W, guide, nullptr, nullptr, ws, s, nullptr, false, true, true);  // trunk only
   if (st) return st;
   const lnm_net_s* net = ad->net;
   const int n_conv = (int)net->layers.size() - 1;

@@ -154,7 +154,16 @@ struct ConvArgs {
   const void* w0;
   const float* b0;
   float w0_out_inv;
+  // fp32: the products on the bf16 matrix cores as three-piece splits
+  // (conv_split.hip) instead of the fp32 matrix instruction
+  int split;
+  // data gradients (split, plain input): where the outputs go (Route)
+  int route;
+  const float *y0, *y1;  // outputs of the layers whose ReLU (and pooling) the gradient passes
+  float *g0, *g1;        // those layers' gradients
+  int c_skip;            // R_CONCAT: channels of the skip connection
 };
+enum Route : int { R_NONE = 0, R_MASK = 1, R_POOL = 2, R_CONCAT = 3 };
 // Sum the split partials in split order, then bias, (scale,) ReLU and the
 // output conversion of out_type (0 fp32, 1 bf16, 2 fp8; 3: fp8 partials,
 // scaled like 2, stored as bf16).
@@ -173,6 +182,7 @@ struct HeadFuse;
 // head: the layer's epilogue also applies the 1x1 head (plain-input layers
 // of at most 32 output channels, unsplit), instead of storing the layer
 hipError_t launch_conv3x3_f32(int mode, int ck, const ConvArgs& a, hipStream_t s, const HeadFuse* head = nullptr);
+hipError_t launch_conv3x3_split(int mode, const ConvArgs& a, hipStream_t s, const HeadFuse* head);
 hipError_t launch_conv3x3_bf16(int mode, const ConvArgs& a, hipStream_t s, const HeadFuse* head = nullptr);
 hipError_t launch_conv3x3_fp8(int mode, const ConvArgs& a, hipStream_t s, const HeadFuse* head = nullptr);
 constexpr int kAmaxBlocks = 256;
@@ -359,10 +369,13 @@ struct Plan {
 Plan plan_workspace(const lnm_net_s* net, int B, int H, int W);
 // comp (batch 1): shade each pixel in the head launch as well.  fuse_head:
 // an fp32 network may apply the head in its last conv layer's epilogue (that
-// layer's output is then not stored; callers that read it pass false)
+// layer's output is then not stored; callers that read it pass false).
+// split: an fp32 network's products as bf16 splits (inference); training's
+// forward pass and the calibration keep the fp32 instruction's sums, which
+// decide ReLU masks and fp8 scales, as they were
 lnm_status run_unet(lnm_ctx_s* ctx, const lnm_net_s* net, int B, int H, int W, const float* guide, float* lm,
                     float* logits, char* ws, hipStream_t s, const CompositeArgs* comp = nullptr,
-                    bool fuse_head = false, bool fuse_first = false);
+                    bool fuse_head = false, bool fuse_first = false, bool split = false);
 lnm_status check_infer(const lnm_net_s* net, int B, int H, int W, size_t ws_bytes, const void* ws);
 // lnm_frame on a caller's (or the library's static) workspace, and its size
 lnm_status frame_impl(lnm_ctx_s* ctx, const lnm_net_s* net, const lnm_volume* vol, const lnm_camera* cam,
@@ -396,13 +409,9 @@ WgradTiling wgrad_tiling(int co, int ci, int B, int h, int w);
 hipError_t launch_wgrad3x3(int mode, const WgradArgs& a, int* n_partials, hipStream_t s);
 hipError_t launch_loss(const float* y, const float* t, float* dz, float* partial, long n, float* loss,
                        hipStream_t s);
-hipError_t launch_relu_mask(float* g, const float* y, long n, hipStream_t s);
 // partial: kHeadBwdBlocks (6 C + 6) floats
 hipError_t launch_head_bwd(const float* dz, const float* w, const float* x, long P, int C, float* e_out,
                            float* grad_w, float* grad_b, float* partial, hipStream_t s);
-hipError_t launch_route_concat(const float* dx, int B, int H, int W, int c0, int c1, float* g_skip, float* g_low,
-                               hipStream_t s);
-hipError_t launch_route_pool(const float* dx, const float* y, int B, int h, int w, int c, float* g, hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, long n, float lr, float b1, float b2, float eps,
                        int t, hipStream_t s);
 // Repack flat parameters into the fp32 forward layout (dgrad = 0) or the
@@ -422,7 +431,6 @@ struct lnm_trainer_s {
   std::vector<size_t> flat_w, flat_b;  // per layer offsets (floats) in the flat vector
   std::vector<lnm::LayerDesc> dgrad;   // transposed layout per layer (layer 0 unused)
   std::vector<size_t> dgrad_off;       // byte offset of each transposed weight block in the state
-  float* zeros;          // zero bias for the data-gradient convolutions
   int step;
   // channel adapters trained with the network (attached before the first
   // step): width, parameter count, flat parameters, gradient, Adam moments

@@ -47,11 +47,6 @@ __global__ __launch_bounds__(256) void finish_sum(const float* __restrict__ part
   if (threadIdx.x == 0) *out = acc * scale;
 }
 
-__global__ __launch_bounds__(256) void relu_mask(float* __restrict__ g, const float* __restrict__ y, long n) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n && !(y[i] > 0.0f)) g[i] = 0.0f;
-}
-
 // Head (1x1, C -> 6) backward in one pass over its input X: the data gradient
 // with X's ReLU mask, E[p][c] = (sum_o W[o][c] dz[p][o]) * (X[p][c] > 0), and
 // the weight and bias sums dz^T X of the block's pixels.  A block takes one
@@ -123,56 +118,6 @@ __global__ __launch_bounds__(256) void head_bwd_finish(const float* __restrict__
     gb[q - 6 * C] = v;
 }
 
-// Gradient of concat(skip, upsample2(low)): the first c0 channels go to the
-// skip, the rest are summed over each 2x2 block into the low-resolution map.
-__global__ __launch_bounds__(256) void route_concat_skip(const float* __restrict__ dx, long P, int c0, int c1,
-                                                          float* __restrict__ g_skip) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= P * c0) return;
-  const long p = i / c0;
-  g_skip[i] = dx[p * (c0 + c1) + (i - p * c0)];
-}
-
-__global__ __launch_bounds__(256) void route_concat_low(const float* __restrict__ dx, int B, int H, int W, int c0,
-                                                         int c1, float* __restrict__ g_low) {
-  const int h = H >> 1, w = W >> 1;
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long)B * h * w * c1) return;
-  const int c = i % c1;
-  const long q = i / c1;
-  const int xx = q % w, yy = (q / w) % h, b = q / ((long)w * h);
-  const int ct = c0 + c1;
-  float s = 0.0f;
-#pragma unroll
-  for (int dy = 0; dy < 2; ++dy)
-#pragma unroll
-    for (int dx2 = 0; dx2 < 2; ++dx2)
-      s += dx[((size_t)(b * H + 2 * yy + dy) * W + 2 * xx + dx2) * ct + c0 + c];
-  g_low[i] = s;
-}
-
-// 2x2 max-pool backward: the gradient of each pooled element is added at the
-// first maximum of its window in raster order.
-__global__ __launch_bounds__(256) void route_pool(const float* __restrict__ dx, const float* __restrict__ y, int B,
-                                                   int h, int w, int C, float* __restrict__ g) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (long)B * h * w * C) return;
-  const int c = i % C;
-  const long q = i / C;
-  const int xx = q % w, yy = (q / w) % h, b = q / ((long)w * h);
-  const int W2 = 2 * w;
-  size_t best = ((size_t)(b * 2 * h + 2 * yy) * W2 + 2 * xx) * C + c;
-  float m = y[best];
-  const size_t cand[3] = {best + C, best + (size_t)W2 * C, best + (size_t)W2 * C + C};
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-    if (y[cand[k]] > m) {
-      m = y[cand[k]];
-      best = cand[k];
-    }
-  g[best] += dx[i];
-}
-
 __global__ __launch_bounds__(256) void adam_kernel(float* __restrict__ p, const float* __restrict__ g,
                                                     float* __restrict__ m, float* __restrict__ v, long n, float lr,
                                                     float b1, float b2, float eps, float c1, float c2) {
@@ -226,11 +171,6 @@ hipError_t launch_loss(const float* y, const float* t, float* dz, float* partial
   return hipGetLastError();
 }
 
-hipError_t launch_relu_mask(float* g, const float* y, long n, hipStream_t s) {
-  hipLaunchKernelGGL(relu_mask, dim3((n + 255) / 256), dim3(256), 0, s, g, y, n);
-  return hipGetLastError();
-}
-
 hipError_t launch_head_bwd(const float* dz, const float* w, const float* x, long P, int C, float* e_out,
                            float* grad_w, float* grad_b, float* partial, hipStream_t s) {
   if (C < 1 || C > 256) return hipErrorInvalidValue;
@@ -238,21 +178,6 @@ hipError_t launch_head_bwd(const float* dz, const float* w, const float* x, long
   hipLaunchKernelGGL(head_bwd, dim3(blocks), dim3(256), sizeof(float) * (256 / C) * n, s, dz, w, x, P, C, e_out,
                      partial);
   hipLaunchKernelGGL(head_bwd_finish, dim3((n + 31) / 32), dim3(256), 0, s, partial, blocks, C, grad_w, grad_b);
-  return hipGetLastError();
-}
-
-hipError_t launch_route_concat(const float* dx, int B, int H, int W, int c0, int c1, float* g_skip, float* g_low,
-                               hipStream_t s) {
-  const long P = (long)B * H * W;
-  hipLaunchKernelGGL(route_concat_skip, dim3((P * c0 + 255) / 256), dim3(256), 0, s, dx, P, c0, c1, g_skip);
-  const long nl = (long)B * (H / 2) * (W / 2) * c1;
-  hipLaunchKernelGGL(route_concat_low, dim3((nl + 255) / 256), dim3(256), 0, s, dx, B, H, W, c0, c1, g_low);
-  return hipGetLastError();
-}
-
-hipError_t launch_route_pool(const float* dx, const float* y, int B, int h, int w, int c, float* g, hipStream_t s) {
-  const long n = (long)B * h * w * c;
-  hipLaunchKernelGGL(route_pool, dim3((n + 255) / 256), dim3(256), 0, s, dx, y, B, h, w, c, g);
   return hipGetLastError();
 }
 

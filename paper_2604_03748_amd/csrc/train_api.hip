@@ -37,12 +37,11 @@ std::vector<ConvStep> schedule(int L) {
 }
 
 struct StateLayout {
-  size_t p, g, m, v, net, zeros, bytes;
+  size_t p, g, m, v, net, bytes;
   std::vector<size_t> dgrad_w;
   std::vector<LayerDesc> fwd, dg;
   size_t net_bytes;
   size_t n_params;
-  int max_dg_co_pad;
 };
 
 bool state_layout(int levels, int base, StateLayout* s, std::string* why) {
@@ -63,7 +62,6 @@ bool state_layout(int levels, int base, StateLayout* s, std::string* why) {
   s->net = take(s->net_bytes);
   s->dg.assign(s->fwd.size(), LayerDesc{});
   s->dgrad_w.assign(s->fwd.size(), 0);
-  s->max_dg_co_pad = 32;
   for (size_t i = 1; i + 1 < s->fwd.size(); ++i) {
     const LayerDesc& f = s->fwd[i];
     LayerDesc d{};
@@ -77,9 +75,7 @@ bool state_layout(int levels, int base, StateLayout* s, std::string* why) {
     d.out_es = 4;
     s->dg[i] = d;
     s->dgrad_w[i] = take(sizeof(float) * d.co_pad * d.ci_pad * 9);
-    s->max_dg_co_pad = std::max(s->max_dg_co_pad, d.co_pad);
   }
-  s->zeros = take(sizeof(float) * s->max_dg_co_pad);
   s->bytes = align256(off);
   return true;
 }
@@ -93,7 +89,7 @@ struct AdapterTrainPlan {
 
 struct TrainPlan {
   Plan fwd;
-  size_t g_base, lm, dz, dx, part, bpart, headpart, losspart, loss, bytes;
+  size_t g_base, lm, dz, part, bpart, headpart, losspart, loss, bytes;
   AdapterTrainPlan ad;
 };
 
@@ -112,16 +108,14 @@ TrainPlan train_plan(const lnm_net_s* net, int B, int H, int W, int ad_c = 0) {
   const size_t P = (size_t)B * H * W;
   t.lm = take(sizeof(float) * P * 6);
   t.dz = take(sizeof(float) * P * 6);
-  size_t dx = 0, part = 0, bpart = 0;
+  size_t part = 0, bpart = 0;
   for (size_t i = 0; i < sch.size(); ++i) {
     const LayerDesc& d = net->layers[i];
     const int h = H >> sch[i].level, w = W >> sch[i].level;
-    if (sch[i].mode == G_POOL || sch[i].mode == G_CONCAT_UP) dx = std::max(dx, (size_t)B * h * w * d.ci);
     const WgradTiling wt = wgrad_tiling(d.co, d.ci, B, h, w);
     part = std::max(part, (size_t)wt.groups * wt.co_pad * 9 * wt.ci_pad);
     bpart = std::max(bpart, (size_t)wt.groups * wt.co_pad);
   }
-  t.dx = take(sizeof(float) * std::max<size_t>(dx, 1));
   t.part = take(sizeof(float) * part);
   t.bpart = take(sizeof(float) * bpart);
   t.headpart = take(sizeof(float) * kHeadBwdBlocks * (6 * (size_t)net->layers.back().ci + 6));
@@ -191,7 +185,6 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
   float* dz = reinterpret_cast<float*>(ws + tp.dz);
   auto Y = [&](int i) { return reinterpret_cast<float*>(ws + tp.fwd.out_off[i]); };
   auto G = [&](int i) { return reinterpret_cast<float*>(ws + tp.g_base + tp.fwd.out_off[i]); };
-  float* dx = reinterpret_cast<float*>(ws + tp.dx);
   float* part = reinterpret_cast<float*>(ws + tp.part);
   float* bpart = reinterpret_cast<float*>(ws + tp.bpart);
 
@@ -259,8 +252,6 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
     const LayerDesc& d = net->layers[i];
     const ConvStep& c = sch[i];
     const int h = H >> c.level, w = W >> c.level;
-    const long n_out = (long)B * h * w * d.co;
-    if (i != last) LNM_HIP_CHECK(launch_relu_mask(G(i), Y(i), n_out, s));  // dL/d(pre-activation)
     // the layer's input exactly as the forward gather read it
     ConvArgs x{};
     x.src0 = c.src0 < 0 ? static_cast<const void*>(guide) : Y(c.src0);
@@ -286,7 +277,9 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
     }
     if (i == 0) break;
     // gradient with respect to the layer's input: the convolution with the
-    // transposed, tap-mirrored weights
+    // transposed, tap-mirrored weights, its outputs passed on through the
+    // pooling, concatenation and ReLU of the layers below (every layer's
+    // gradient is masked where its last part arrives)
     const LayerDesc& dg = tr->dgrad[i];
     ConvArgs a{};
     a.src0 = G(i);
@@ -297,21 +290,19 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
     a.ci_pad = dg.ci_pad;
     a.co = dg.co;
     a.w = tr->state + tr->dgrad_off[i];
-    a.bias = tr->zeros;
-    a.out = c.mode == G_PLAIN ? static_cast<void*>(G(c.src0)) : static_cast<void*>(dx);
-    a.relu = 0;
     a.n_tiles = dg.co_pad / kBN;
     a.splits = 1;
-    {
-      ProfScope ps(ctx, LNM_K_CONV, s);
-      LNM_HIP_CHECK(launch_conv3x3_f32(G_PLAIN, 16, a, s));
+    a.split = 1;
+    a.route = c.mode == G_PLAIN ? R_MASK : c.mode == G_POOL ? R_POOL : R_CONCAT;
+    a.y0 = Y(c.src0);
+    a.g0 = G(c.src0);
+    if (c.mode == G_CONCAT_UP) {
+      a.c_skip = net->layers[c.src0].co;
+      a.y1 = Y(c.src1);
+      a.g1 = G(c.src1);
     }
-    if (c.mode == G_POOL) {
-      LNM_HIP_CHECK(launch_route_pool(dx, Y(c.src0), B, h, w, d.ci, G(c.src0), s));
-    } else if (c.mode == G_CONCAT_UP) {
-      LNM_HIP_CHECK(launch_route_concat(dx, B, h, w, net->layers[c.src0].co, net->layers[c.src1].co, G(c.src0),
-                                        G(c.src1), s));
-    }
+    ProfScope ps(ctx, LNM_K_CONV, s);
+    LNM_HIP_CHECK(launch_conv3x3_f32(G_PLAIN, 16, a, s));
   }
   return LNM_OK;
 }
@@ -371,7 +362,6 @@ lnm_status lnm_trainer_create(lnm_ctx ctx, int32_t levels, int32_t base, const f
   tr->net.dev_bytes = sl.net_bytes;
   tr->dgrad = sl.dg;
   tr->dgrad_off = sl.dgrad_w;
-  tr->zeros = reinterpret_cast<float*>(st + sl.zeros);
   tr->step = 0;
   size_t off = 0;
   for (auto& d : sl.fwd) {
@@ -385,7 +375,6 @@ lnm_status lnm_trainer_create(lnm_ctx ctx, int32_t levels, int32_t base, const f
   if (e == hipSuccess) e = hipMemsetAsync(tr->g, 0, sizeof(float) * n_params, s);
   if (e == hipSuccess) e = hipMemsetAsync(tr->m, 0, sizeof(float) * n_params, s);
   if (e == hipSuccess) e = hipMemsetAsync(tr->v, 0, sizeof(float) * n_params, s);
-  if (e == hipSuccess) e = hipMemsetAsync(tr->zeros, 0, sizeof(float) * sl.max_dg_co_pad, s);
   if (e != hipSuccess) {
     delete tr;
     return fail(LNM_ERR_DEVICE, std::string("trainer upload: ") + hipGetErrorString(e));
@@ -544,7 +533,7 @@ lnm_status lnm_trainer_infer(lnm_ctx ctx, lnm_trainer tr, int32_t batch, int32_t
   lnm_status st = check_infer(&tr->net, batch, H, W, ws_bytes, workspace);
   if (st) return st;
   return run_unet(ctx, &tr->net, batch, H, W, guide, lightmaps, nullptr, static_cast<char*>(workspace),
-                  (hipStream_t)stream, nullptr, false, true);
+                  (hipStream_t)stream, nullptr, false, true, true);
 }
 
 }  // extern "C"
