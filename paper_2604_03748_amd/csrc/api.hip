@@ -393,6 +393,7 @@ lnm_status run_unet(lnm_ctx_s* ctx, const lnm_net_s* net, int B, int H, int W, c
     const LayerTiling tl = conv_layer_tiling(net, li, B, a.H, a.W);
     a.th = tl.th;
     a.splits = tl.splits;
+    a.seq = tl.seq;
     a.partial = reinterpret_cast<float*>(ws + p.partial_off);
     ++li;
     ProfScope ps(ctx, LNM_K_CONV, s);
@@ -411,7 +412,7 @@ lnm_status run_unet(lnm_ctx_s* ctx, const lnm_net_s* net, int B, int H, int W, c
     return err;
   };
   // inference: the last layer's epilogue applies the head (and the frame's
-  // shading) when its one 32-channel tile is unsplit, so the layer's output
+  // shading) when one unsplit tile holds its channels, so the layer's output
   // is never stored and the head needs no launch of its own; the head reads
   // the activations in the precision they would have been stored in, so the
   // result equals the separate head kernel's
@@ -424,18 +425,16 @@ lnm_status run_unet(lnm_ctx_s* ctx, const lnm_net_s* net, int B, int H, int W, c
   if (comp) hf.comp = *comp;
   const bool last_e4m3 = net->layers[n_conv - 1].out_es == 1;  // features the head reads
   hf.in_scale = last_e4m3 ? net->act_scale[n_conv - 1] : 1.0f;
-  const bool fused = fuse_head && lm && !logits && net->layers[n_conv - 1].co <= kBN &&
-                     layer_splits(net, n_conv - 1, B, H, W) == 1;
-  // the first two layers in one launch (fp32, fp8, or bf16 in the default
-  // tile form): the second recomputes the first's outputs on its tiles
-  // (their halo included) from the guide, so the first layer's output is
-  // neither stored nor read
+  const LayerDesc& ld = net->layers[n_conv - 1];
+  const LayerTiling lt = conv_layer_tiling(net, n_conv - 1, B, H, W);
+  const bool fused = fuse_head && lm && !logits && ld.co <= (ld.prec == LNM_BF16 ? 48 : kBN) && lt.splits == 1 &&
+                     lt.seq == 1;
+  // the first two layers in one launch: the second recomputes the first's
+  // outputs on its tiles (their halo included) from the guide, so the first
+  // layer's output is neither stored nor read (bf16 and fp8 networks only
+  // run this way)
   const LayerDesc &d0 = net->layers[0], &d1 = net->layers[1];
-  const bool first =
-      fuse_first && ((d0.prec == LNM_FP32 && d1.prec == LNM_FP32 && d0.ck == 4 && d1.ck == 16) ||
-                     (d0.prec == LNM_BF16 && d1.prec == LNM_BF16 &&
-                      conv_layer_tiling(net, 1, B, H, W).th != kBf16Large) ||
-                     (d0.prec == LNM_FP8_E4M3 && d1.prec == LNM_FP8_E4M3 && d0.out_es == 1));
+  const bool first = d0.prec != LNM_FP32 || (fuse_first && d0.ck == 4 && d1.ck == 16);
   hipError_t e;
   const void* x = guide;
   int cx = 3;

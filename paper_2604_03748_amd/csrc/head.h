@@ -46,19 +46,19 @@ __device__ __forceinline__ void shade_pixel(const CompositeArgs& a, int p, const
   shade_lights(a.l, a.rgb, 0, a.n_lights, a.guide, a.rgba, (size_t)p, L);
 }
 
-// Head epilogue of a conv layer (one 32-channel output tile): the tile's
-// stored-precision activations are in sh[pixel][33] (pixels of the TH x 16
-// tile in row order) and the head weights in shw[6][32] (zero past the
+// Head epilogue of a conv layer (one tile of NC output channels): the tile's
+// stored-precision activations are in sh[pixel][NC + 1] (pixels of the TH x 16
+// tile in row order) and the head weights in shw[6][NC] (zero past the
 // layer's channels), after a barrier.  Two lanes finish each pixel, lane
 // t < TH * 16 outputs 0..2 and lane t + TH * 16 outputs 3..5: the sums in
 // channel order (as the separate head kernel forms them), the sigmoid, the
 // lightmap store and, when asked, the decode to linear; the first lane then
 // shades the pixel from the six linear values, exchanged through sh.  Every
 // lane of the workgroup calls it (it has barriers).
-template <int TH>
+template <int TH, int NC = 32>
 __device__ __forceinline__ void head_finish(const HeadFuse& hf, float* sh, const float* shw, int b, int H, int W,
                                             int y0, int x0) {
-  constexpr int kTileW = 16, kPP = 33, NP = TH * kTileW;
+  constexpr int kTileW = 16, kPP = NC + 1, NP = TH * kTileW;
   static_assert(2 * NP <= 256, "two lanes per pixel");
   const int t = threadIdx.x, tp = t % NP, half = t / NP;
   const bool act = t < 2 * NP;
@@ -71,10 +71,10 @@ __device__ __forceinline__ void head_finish(const HeadFuse& hf, float* sh, const
     float z[3];
 #pragma unroll
     for (int j = 0; j < 3; ++j) z[j] = hf.b[3 * half + j];
-    for (int c = 0; c < 32; c += 4) {
+    for (int c = 0; c < NC; c += 4) {
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        const float* w = shw + (3 * half + j) * 32 + c;
+        const float* w = shw + (3 * half + j) * NC + c;
         z[j] += w[0] * v[c] + w[1] * v[c + 1] + w[2] * v[c + 2] + w[3] * v[c + 3];
       }
     }
@@ -101,8 +101,9 @@ __device__ __forceinline__ void head_finish(const HeadFuse& hf, float* sh, const
 }
 
 // Head weights into LDS: shw[o][n] = w[o][n] for n < co, else 0.
+template <int NC = 32>
 __device__ __forceinline__ void head_weights(const HeadFuse& hf, int co, float* shw) {
-  for (int q = threadIdx.x; q < 6 * 32; q += blockDim.x) shw[q] = (q % 32) < co ? hf.w[(q / 32) * co + q % 32] : 0.0f;
+  for (int q = threadIdx.x; q < 6 * NC; q += blockDim.x) shw[q] = (q % NC) < co ? hf.w[(q / NC) * co + q % NC] : 0.0f;
 }
 
 }  // namespace lnm

@@ -144,9 +144,8 @@ struct ConvArgs {
   // launch_splitk_reduce finishes the layer
   int n_tiles, splits;
   float* partial;
-  int th;  // tile height in rows: 4 or 8 (0 means 8; the input layer always 8); kBf16Large: the
-           // bf16 large-layer form (kBf16LargeRows rows x 64 channels per workgroup; n_tiles >= 2,
-           // no head)
+  int seq;  // bf16, fp8: > 1 with splits == 1: the splits run one after the other in each workgroup
+  int th;   // tile height in rows: 4 or 8 (0 means 8)
   int out_bf16;  // fp8 layers: store max(y, 0) as bf16 (unscaled) instead of e4m3
   // G_FIRST: src0 is the guide and the layer's input is the network's first
   // layer, recomputed per tile from its packed weights and bias (fp8: stored
@@ -171,12 +170,11 @@ hipError_t launch_splitk_reduce(const ConvArgs& a, int out_type, hipStream_t s);
 // Splits for a layer launched with `wgs` workgroups over `nchunks` input chunks.
 int conv_splits(long wgs, int nchunks, int target);
 // Tile height (4 or 8 rows) and split-K factor of conv layer i of `net` at
-// level size h x w and batch B.
+// level size h x w and batch B; seq: the factor when the splits run one after
+// the other in each workgroup (splits is then 1).
 struct LayerTiling {
-  int th, splits;
+  int th, splits, seq;
 };
-// The bf16 large-layer tile (ConvArgs::th code and its height in rows).
-constexpr int kBf16Large = 16, kBf16LargeRows = 8;
 LayerTiling conv_layer_tiling(const lnm_net_s* net, int i, int B, int h, int w);
 struct HeadFuse;
 // head: the layer's epilogue also applies the 1x1 head (plain-input layers

@@ -112,35 +112,29 @@ int conv_splits(long wgs, int nchunks, int target) {
 // tiles leave one workgroup per CU (nothing else on the CU hides a
 // workgroup's chunk-boundary stalls): 5 us per fp32 frame, 9 us per bf16
 // frame.  fp8 layers, whose LDS footprint lets five 4-row workgroups share
-// a CU, take 4-row tiles throughout: 19 us per frame.  Large bf16 layers
-// take the 8-row x 64-channel form when it still gives two workgroups per
-// CU.
+// a CU, take 4-row tiles throughout: 19 us per frame.
 //
 // The split and the tile height follow the workgroup count of one image, so
 // an image's sums (whose order the split sets) are the same alone and in any
-// batch; only the bf16 large form, which sums in the same order as the
-// default form, looks at the batch.
+// batch.  Where a batch fills the chip without the split (two 8-row
+// workgroups per CU), bf16 and fp8 layers run their splits one after the
+// other in each workgroup: the same sums without the partial tensors (16 x
+// 256^2, 4-level base-32 bf16: 84 us of reductions and the partial stores).
 LayerTiling conv_layer_tiling(const lnm_net_s* net, int i, int B, int h, int w) {
   const LayerDesc& d = net->layers[i];
-  if (d.ci == 3) return {8, 1};
+  if (d.ci == 3) return {8, 1, 1};
   const int target = d.prec == LNM_FP32 ? 256 : 512, nch = d.ci_pad / d.ck;
   auto wgs = [&](int th) { return (long)((w + 15) / 16) * ((h + th - 1) / th) * (d.co_pad / kBN); };
   const int s8 = conv_splits(wgs(8), nch, target);
-  if (d.prec == LNM_BF16 && s8 == 1) {
-    // large bf16 layers: the 64-channel tile, when it still gives two
-    // workgroups per CU
-    const int nt = d.co_pad / kBN;
-    const long large =
-        (long)((w + 15) / 16) * ((h + kBf16LargeRows - 1) / kBf16LargeRows) * B * ((nt + 1) / 2);
-    if (nt >= 2 && large >= 512) return {kBf16Large, 1};
-  }
+  LayerTiling t{8, s8, 1};
   const bool fp8 = d.prec == LNM_FP8_E4M3;
   if (s8 > 1 || wgs(8) <= 256 || fp8) {
     // the longest fp32 layers (16+ chunks) split on to two workgroups per CU
     const int s4 = conv_splits(wgs(4), nch, d.prec == LNM_FP32 && nch >= 16 ? 512 : target);
-    if (s4 < s8 || wgs(8) <= 256 || fp8) return {4, s4};
+    if (s4 < s8 || wgs(8) <= 256 || fp8) t = {4, s4, 1};
   }
-  return {8, s8};
+  if (t.splits > 1 && d.prec != LNM_FP32 && B * wgs(8) >= 512) t = {8, 1, t.splits};
+  return t;
 }
 
 // Weight gradient of a layer: 32 x 32 channels per workgroup (16 where the
