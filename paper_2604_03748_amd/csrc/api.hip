@@ -127,7 +127,20 @@ static lnm_status march_setup(const lnm_volume* vol, const lnm_camera* cam, cons
     return fail(LNM_ERR_UNSUPPORTED, "params.work_order: a z cell's two grid planes do not fit in LDS");
   m->brick = vol->bricks;  // NULL: launch_march builds them in its scratch
   m->nbx = m->nby = m->nbz = 0;
+  m->pair = nullptr;
+  m->pairs = march_pairs(*m, c->W, c->H);
   return LNM_OK;
+}
+
+// Scratch of a march in a workspace of ws_bytes: without the plane pairs when
+// only that fits (the same guiding map from the bricks).
+static size_t fit_march(MarchDev* m, int K, int W, int H, size_t ws_bytes) {
+  size_t need = march_scratch_bytes(*m, K, W, H);
+  if (ws_bytes < need && m->pairs) {
+    m->pairs = 0;
+    need = march_scratch_bytes(*m, K, W, H);
+  }
+  return need;
 }
 
 // ---------------------------------------------------------------- network
@@ -529,7 +542,7 @@ lnm_status frame_impl(lnm_ctx_s* ctx, const lnm_net_s* net, const lnm_volume* vo
   st = check_infer(net, 1, c.H, c.W, ws_bytes, workspace);
   if (st) return st;
   const int K = march_capacity(m);
-  const size_t need = march_scratch_bytes(m, K, c.W, c.H);
+  const size_t need = fit_march(&m, K, c.W, c.H, ws_bytes);
   if (ws_bytes < need) return fail(LNM_ERR_SHAPE, "workspace too small for the march: need " + std::to_string(need));
   CompositeArgs a{};
   if (rgba) {
@@ -658,7 +671,7 @@ lnm_status lnm_march(lnm_ctx ctx, const lnm_volume* vol, const lnm_camera* cam, 
   lnm_status st = march_setup(vol, cam, prm, &m, &c);
   if (st) return st;
   const int K = march_capacity(m);
-  const size_t need = march_scratch_bytes(m, K, c.W, c.H);
+  const size_t need = fit_march(&m, K, c.W, c.H, ws_bytes);
   if (!workspace || ws_bytes < need)
     return fail(LNM_ERR_SHAPE, "march workspace too small: need " + std::to_string(need) + " bytes");
   ProfScope ps(ctx, LNM_K_MARCH, (hipStream_t)stream);
@@ -691,7 +704,7 @@ lnm_status lnm_march_batch(lnm_ctx ctx, int32_t n, const lnm_volume* vols, const
     if (!guides[i]) return fail(LNM_ERR_ARG, "guides[" + std::to_string(i) + "] is NULL");
     const lnm_status st = march_setup(vols + i, cams + i, prms + i, &ms[i], &cs[i]);
     if (st) return fail(st, "march " + std::to_string(i) + ": " + g_err);
-    need = std::max(need, march_scratch_bytes(ms[i], march_capacity(ms[i]), cs[i].W, cs[i].H));
+    need = std::max(need, fit_march(&ms[i], march_capacity(ms[i]), cs[i].W, cs[i].H, ws_bytes));
   }
   if (!workspace || ws_bytes < need)
     return fail(LNM_ERR_SHAPE, "march workspace too small: need " + std::to_string(need) + " bytes");

@@ -48,6 +48,11 @@ struct MarchDev {
   int zorder;        // order of the light marches (march_order): bands, z layers or z cells
   const float* brick;  // bricked copy of rho (4^3 cells + apron per 128-float slot); caller's or scratch
   int nbx, nby, nbz;   // bricks per axis
+  // z order: the march reads plane pairs instead of bricks (march_pairs):
+  // entry ((k (ny + 2) + j) (nx + 2) + i) is the two values of grid planes
+  // k - 1 and k at column (i - 1, j - 1), zero outside the grid
+  int pairs;
+  const float* pair;  // in the scratch
 };
 
 struct MarchBuf {
@@ -65,6 +70,7 @@ struct MarchBuf {
   int2* srt;    // z order: [P * K] the records of all bands in z-bucket order, else NULL
   float* brick;
   int nbx, nby, nbz;
+  float* pair;
   int K, P;  // capacity per pixel, pixels
 };
 
@@ -100,7 +106,11 @@ int march_capacity(const MarchDev& m);
 // fit in LDS, else bands; -1 when LNM_ORDER_CELLS does not fit.
 constexpr int kOrderBands = 0, kOrderLayers = 1, kOrderCells = 2;
 int march_order(int work_order, int light_set, int nx, int ny, int nz);
-// Scratch of one march; the bricked grid is part of it unless m.brick is set.
+// Whether a march of a W x H view should read plane pairs, and their bytes.
+bool march_pairs(const MarchDev& m, int W, int H);
+size_t pairs_bytes(int nx, int ny, int nz);
+// Scratch of one march; the plane pairs are part of it when m.pairs is set,
+// else the bricked grid unless m.brick is.
 size_t march_scratch_bytes(const MarchDev& m, int K, int W, int H);
 MarchBuf march_buffers(void* ws, const MarchDev& m, int K, int W, int H);
 size_t bricks_bytes(int nx, int ny, int nz);

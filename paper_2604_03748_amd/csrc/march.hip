@@ -2,7 +2,8 @@
 // reference lightmaps, fp32.
 //
 // The march first copies the density grid into 4^3-cell bricks (so the 8
-// corners of a trilinear sample are one short span of one 512-byte slot),
+// corners of a trilinear sample are one short span of one 512-byte slot) or,
+// for large grids, into plane pairs (two 16-byte loads per sample),
 // cutting the screen's 8x8 tiles into eight bands of equal estimated work on
 // the way, then runs three kernels (see march_primary): the primary march
 // (four lanes per pixel, one band per XCD), the light marches (one lane per
@@ -144,6 +145,31 @@ __device__ __forceinline__ float brick_lerp_flat(const MarchDev& m, const BrickT
 __device__ __forceinline__ float sample_sigma(const MarchDev& m, float px, float py, float pz) {
   const BrickTap t = brick_tap(m, px, py, pz);
   return brick_lerp(m, t, brick_load(t));
+}
+
+// The same value from the plane pairs: the cell's eight corners as two
+// 16-byte loads (rows j and j + 1: two neighbouring pairs each), the taps,
+// fractions, mask and interpolation of the bricks.
+struct PairVals {
+  float r0[4], r1[4];  // (below, above) at i and i + 1, rows j and j + 1
+};
+__device__ __forceinline__ PairVals pair_load(const MarchDev& m, uint32_t at) {
+  const char* p = reinterpret_cast<const char*>(m.pair);
+  PairVals c;
+  __builtin_memcpy(c.r0, p + 8u * at, 16);
+  __builtin_memcpy(c.r1, p + sizeof(float2) * (m.nx + 2) + 8u * at, 16);
+  return c;
+}
+__device__ __forceinline__ float sample_sigma_pairs(const MarchDev& m, float px, float py, float pz) {
+  const float gx = fmaf(px, (float)m.nx, -0.5f), gy = fmaf(py, (float)m.ny, -0.5f), gz = fmaf(pz, (float)m.nz, -0.5f);
+  const bool inside = gx > -1.0f && gy > -1.0f && gz > -1.0f && gx < (float)m.nx && gy < (float)m.ny &&
+                      gz < (float)m.nz;
+  const float cx = inside ? gx : 0.0f, cy = inside ? gy : 0.0f, cz = inside ? gz : 0.0f;
+  const float fx0 = floorf(cx), fy0 = floorf(cy), fz0 = floorf(cz);
+  const uint32_t i = (uint32_t)((int)fx0 + 1), j = (uint32_t)((int)fy0 + 1), k = (uint32_t)((int)fz0 + 1);
+  const PairVals c = pair_load(m, (k * (uint32_t)(m.ny + 2) + j) * (uint32_t)(m.nx + 2) + i);
+  const float v[8] = {c.r0[0], c.r0[2], c.r1[0], c.r1[2], c.r0[1], c.r0[3], c.r1[1], c.r1[3]};
+  return m.sigma_scale * trilerp(v, cx - fx0, cy - fy0, cz - fz0) * (inside ? 1.0f : 0.0f);
 }
 
 // N samples: all addresses, then all loads, then all interpolations.
@@ -352,6 +378,97 @@ __device__ __forceinline__ float light_transmittance_batched(const MarchDev& m, 
   return expf(-acc * h);
 }
 
+// Transmittance toward one light on the plane pairs: the taps, interpolation
+// and sums of light_transmittance_batched, so the same result bit for bit.
+// Samples outside the support box add nothing, and the points of a march
+// move monotonically along every axis (a fused multiply-add rounds
+// monotonically), so when steps 1 and kin lie inside, those between do too
+// and need no tests, selects or masks.  A march whose first step lies outside
+// (a sample within rounding of the box's face) samples each point masked.
+template <bool FLAT>
+__device__ __forceinline__ float light_transmittance_pairs(const MarchDev& m, V3 x, V3 l) {
+  const float h = m.h, lim = m.tau_max / h;
+  auto grid = [&](int k, float* gx, float* gy, float* gz) {
+    const float tt = (float)k * h;
+    *gx = fmaf(fmaf(tt, l.x, x.x), (float)m.nx, -0.5f);
+    *gy = fmaf(fmaf(tt, l.y, x.y), (float)m.ny, -0.5f);
+    *gz = fmaf(fmaf(tt, l.z, x.z), (float)m.nz, -0.5f);
+  };
+  auto inside = [&](int k) {
+    float gx, gy, gz;
+    grid(k, &gx, &gy, &gz);
+    return gx > -1.0f && gy > -1.0f && gz > -1.0f && gx < (float)m.nx && gy < (float)m.ny && gz < (float)m.nz;
+  };
+  int kin = light_steps(m, x, l, h);
+  while (kin > 0 && !inside(kin)) --kin;  // the exit distance is rounded: a step or two
+  if (kin > 0 && !inside(1)) {
+    float acc = 0.0f;
+    for (int k = 1; k <= kin; ++k) {
+      if (!inside(k)) continue;
+      float gx, gy, gz;
+      grid(k, &gx, &gy, &gz);
+      const float fx0 = floorf(gx), fy0 = floorf(gy), fz0 = floorf(gz);
+      const PairVals c = pair_load(m, ((uint32_t)((int)fz0 + 1) * (uint32_t)(m.ny + 2) + (uint32_t)((int)fy0 + 1)) *
+                                              (uint32_t)(m.nx + 2) + (uint32_t)((int)fx0 + 1));
+      const float v[8] = {c.r0[0], c.r0[2], c.r1[0], c.r1[2], c.r0[1], c.r0[3], c.r1[1], c.r1[3]};
+      acc += m.sigma_scale * (FLAT ? flat_lerp(v[0], v[4] - v[0], v[1], v[5] - v[1], v[2], v[6] - v[2], v[3],
+                                               v[7] - v[3], gx - fx0, gy - fy0, gz - fz0)
+                                   : trilerp(v, gx - fx0, gy - fy0, gz - fz0));
+      if (acc > lim) return 0.0f;
+    }
+    return expf(-acc * h);
+  }
+  const uint32_t row = (uint32_t)(m.nx + 2), layer = (uint32_t)(m.ny + 2) * row;
+  float fz = 0.0f;
+  uint32_t zat = 0;
+  if constexpr (FLAT) {  // every sample has the z of x
+    const float gz = fmaf(x.z, (float)m.nz, -0.5f), fz0 = floorf(gz);
+    fz = gz - fz0;
+    zat = kin > 0 ? (uint32_t)((int)fz0 + 1) * layer : 0u;
+  }
+  float acc = 0.0f;
+  for (int k = 1; k <= kin; k += 4) {
+    float f[4][3];
+    PairVals c[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float tt = (float)min(k + q, kin) * h;
+      const float gx = fmaf(fmaf(tt, l.x, x.x), (float)m.nx, -0.5f);
+      const float gy = fmaf(fmaf(tt, l.y, x.y), (float)m.ny, -0.5f);
+      const float fx0 = floorf(gx), fy0 = floorf(gy);
+      f[q][0] = gx - fx0;
+      f[q][1] = gy - fy0;
+      f[q][2] = fz;
+      uint32_t at = (uint32_t)((int)fy0 + 1) * row + (uint32_t)((int)fx0 + 1) + zat;
+      if constexpr (!FLAT) {
+        const float gz = fmaf(fmaf(tt, l.z, x.z), (float)m.nz, -0.5f), fz0 = floorf(gz);
+        f[q][2] = gz - fz0;
+        at += (uint32_t)((int)fz0 + 1) * layer;
+      }
+      c[q] = pair_load(m, at);
+    }
+    __builtin_amdgcn_sched_barrier(0);  // keep the loads ahead of their uses
+    // the depth is tested after each sample, the branch taken once per batch
+    bool over = false;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const PairVals& p = c[q];
+      float s;
+      if constexpr (FLAT) {
+        s = flat_lerp(p.r0[0], p.r0[1] - p.r0[0], p.r0[2], p.r0[3] - p.r0[2], p.r1[0], p.r1[1] - p.r1[0], p.r1[2],
+                      p.r1[3] - p.r1[2], f[q][0], f[q][1], f[q][2]);
+      } else {
+        const float v[8] = {p.r0[0], p.r0[2], p.r1[0], p.r1[2], p.r0[1], p.r0[3], p.r1[1], p.r1[3]};
+        s = trilerp(v, f[q][0], f[q][1], f[q][2]);
+      }
+      acc += k + q <= kin ? m.sigma_scale * s : 0.0f;
+      over |= acc > lim;
+    }
+    if (over) return 0.0f;
+  }
+  return expf(-acc * h);
+}
+
 // The light march of a flat light (no z component) with the density of its
 // sample's z cell staged in LDS: pl[ny + 3][nx + 3] pairs (value of the grid
 // plane below the cell, value above minus value below), index i + 1 holding
@@ -422,15 +539,18 @@ __device__ __forceinline__ float light_transmittance_lds(const MarchDev& m, V3 x
 // block.
 
 // z bucket of a sample point: its trilinear cell k' = floor(gz) + 1 (the
-// cell between grid planes k' - 1 and k'), in z order grouped by brick layer
-// (the bricks hold cells in layers k' / 4), capped at the last bucket.  A
+// cell between grid planes k' - 1 and k'), in z order on bricks grouped by
+// brick layer (the bricks hold cells in layers k' / 4), capped at the last
+// bucket.  (On plane pairs one bucket per cell: 1275 us of light marches and 91
+// of sorting at 256^3 / 1024^2 against 1338 and 83 with layers; a pixel's
+// records kept together instead of its neighbours': 1304 and 131.)  A
 // side light has no z component, so a light march stays in its sample's
 // cell (the fallback lights of a ray along z and the left/right set do not;
 // the order then only loses locality).
 __device__ __forceinline__ int z_bucket(const MarchDev& m, float pz) {
   const float gz = fminf(fmaxf(fmaf(pz, (float)m.nz, -0.5f), -1.0f), (float)m.nz);
   const int cell = (int)floorf(gz) + 1;
-  return min(m.zorder == kOrderCells ? cell : cell >> 2, kZBuckets - 1);
+  return min(m.zorder == kOrderCells || m.pairs ? cell : cell >> 2, kZBuckets - 1);
 }
 
 __device__ __forceinline__ void tile_origin(const TileMap& tm, int L, int* tx, int* ty) {
@@ -480,7 +600,8 @@ __device__ __forceinline__ int wave_max(int v) {
 // The march runs in three kernels so that its dominant cost, the light
 // marches (two per primary sample), is spread over one lane per recorded
 // sample and light instead of serialised inside one lane per pixel:
-//   0. (relayout_balance: the bricked grid, and the band tile ranges)
+//   0. (relayout_balance: the bricked grid, or pairs_balance: the plane pairs;
+//      and the band tile ranges)
 //   1. march_primary: four lanes per pixel walk the primary samples, write
 //      T and D, and record (t_n, A_n, T_{n-1}) of every sample with a
 //      nonzero weight in [k][P] planes (in z order also the sample's z
@@ -508,6 +629,7 @@ __device__ __forceinline__ float depth_step(float L, float sig, float h) { retur
 // starts at `list`, with four lanes per pixel (see below); zh: the block's
 // z-bucket counts, agg: 5 ints of LDS for the block's append.  Every thread
 // of the block calls it (it has block barriers).
+template <bool PAIRS>
 __device__ __forceinline__ void primary_tile(const MarchDev& m, const CamDev& c, const TileMap& tm,
                                              const MarchBuf& buf, float* __restrict__ guide, int tile, int band,
                                              int2* __restrict__ list, int* zh, int* agg) {
@@ -553,7 +675,8 @@ __device__ __forceinline__ void primary_tile(const MarchDev& m, const CamDev& c,
     const int n = nb + s;
     const float t = ((float)n + u) * h;
     const float pz = o.z + t * d.z;
-    const float sg = sample_sigma(m, o.x + t * d.x, o.y + t * d.y, pz);
+    const float sg = PAIRS ? sample_sigma_pairs(m, o.x + t * d.x, o.y + t * d.y, pz)
+                           : sample_sigma(m, o.x + t * d.x, o.y + t * d.y, pz);
     const bool valid = n <= n1;
     const float sig = valid ? sg : 0.0f;
     // running depth through the quad: lane s ends with tau_n
@@ -637,6 +760,7 @@ __device__ __forceinline__ void primary_tile(const MarchDev& m, const CamDev& c,
 // owns.  The band's blocks take its tiles in turn.
 // In z order the block also counts its records per z bucket in LDS and adds
 // them to the global counts at the end.
+template <bool PAIRS>
 __global__ __launch_bounds__(256, 4) void march_primary(MarchDev m, CamDev c, TileMap tm, MarchBuf buf,
                                                      float* __restrict__ guide) {
   __shared__ int zh[kZBuckets];
@@ -650,7 +774,7 @@ __global__ __launch_bounds__(256, 4) void march_primary(MarchDev m, CamDev c, Ti
   const int lo = start[band], hi = start[band + 1];
   int2* list = buf.rec ? buf.rec + (size_t)lo * (kTile * kTile) * (size_t)buf.K : nullptr;
   for (int L = lo + (int)(blockIdx.x >> 3); L < hi; L += slots)
-    primary_tile(m, c, tm, buf, guide, L, band, list, zh, agg);
+    primary_tile<PAIRS>(m, c, tm, buf, guide, L, band, list, zh, agg);
   if (m.zorder) {
     __syncthreads();
     for (int q = threadIdx.x; q < kZBuckets; q += 256)
@@ -750,6 +874,40 @@ __global__ __launch_bounds__(256) void relayout_balance(MarchDev m, CamDev c, Ti
     return;
   }
   relayout_block(m.rho, m.nx, m.ny, m.nz, m.nbx, m.nby, brick, sh.rows, blockIdx.x, blockIdx.y, blockIdx.z - 1);
+}
+
+// Plane pairs from the caller's linear grid: a lane takes one column of the
+// (ny + 2) x (nx + 2) border plane over kPairZ cells, each grid value read once
+// and carried to the next cell, so loads and stores run along x.  As in
+// relayout_balance, one extra z slice in front holds the balance block.
+// Bound by memory (256^3: 67 MB read and 137 MB written in 107 us, as the
+// bricks took).
+constexpr int kPairZ = 8;
+__global__ __launch_bounds__(256) void pairs_balance(MarchDev m, CamDev c, TileMap tm, int* __restrict__ ctr,
+                                                     float* __restrict__ pair) {
+  __shared__ BalanceLds sh;
+  if (blockIdx.y == 0) {
+    if (blockIdx.x == 0) balance_tiles(m, c, tm, ctr, sh);
+    return;
+  }
+  const int row = m.nx + 2, plane = (m.ny + 2) * row;
+  const int e = blockIdx.x * 256 + threadIdx.x, k0 = ((int)blockIdx.y - 1) * kPairZ;
+  if (e >= plane) return;
+  const int j = e / row - 1, i = e - (j + 1) * row - 1;
+  const bool in = i >= 0 && i < m.nx && j >= 0 && j < m.ny;
+  const size_t ps = (size_t)m.nx * m.ny;
+  const float* src = m.rho + (in ? (size_t)j * m.nx + i : 0);
+  float v[kPairZ + 1];  // grid planes k0 - 1 .. k0 + kPairZ - 1
+#pragma unroll
+  for (int q = 0; q <= kPairZ; ++q) {
+    const int k = k0 + q - 1;
+    v[q] = src[(size_t)min(max(k, 0), m.nz - 1) * ps];
+    if (!in || k < 0 || k >= m.nz) v[q] = 0.0f;
+  }
+#pragma unroll
+  for (int q = 0; q < kPairZ; ++q)
+    if (k0 + q <= m.nz)
+      reinterpret_cast<float2*>(pair)[(size_t)(k0 + q) * plane + e] = make_float2(v[q], v[q + 1]);
 }
 
 // Entry r of the band lists concatenated in band order.
@@ -925,7 +1083,7 @@ __global__ __launch_bounds__(256) void zsort_cells(MarchBuf buf) {
 // the bricks in use at a time are about one layer).  Result: T toward the
 // top (or first side) light in tl[0][k][pixel], toward the bottom (second
 // side) light in tl[1][k][pixel].
-template <bool Z>
+template <bool Z, bool PAIRS>
 __global__ __launch_bounds__(256) void march_lights(MarchDev m, CamDev c, MarchBuf buf, int slots) {
   int count[8], total = 0;
 #pragma unroll
@@ -956,8 +1114,12 @@ __global__ __launch_bounds__(256) void march_lights(MarchDev m, CamDev c, MarchB
       V3 l = side_light(d, m.light_set);
       if (light) l = v3(-l.x, -l.y, -l.z);
       const V3 x = v3(o.x + t * d.x, o.y + t * d.y, o.z + t * d.z);
-      buf.tl[(size_t)light * buf.K * buf.P + q] =
-          l.z == 0.0f ? light_transmittance_batched<true>(m, x, l) : light_transmittance_batched<false>(m, x, l);
+      float T;
+      if constexpr (PAIRS)
+        T = l.z == 0.0f ? light_transmittance_pairs<true>(m, x, l) : light_transmittance_pairs<false>(m, x, l);
+      else
+        T = l.z == 0.0f ? light_transmittance_batched<true>(m, x, l) : light_transmittance_batched<false>(m, x, l);
+      buf.tl[(size_t)light * buf.K * buf.P + q] = T;
     } while (0);
     if constexpr (Z) {
       if (R >= units) break;
@@ -1414,13 +1576,14 @@ static TileMap tile_map(const CamDev& c) {
 
 // Light-march blocks per XCD in z order: as many as are resident at once
 // (the occupancy of march_lights on one XCD's CUs), at least one.
+template <bool PAIRS>
 static int light_blocks_per_xcd() {
   static int n = 0;
   if (n == 0) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, march_lights<true>, 256, 0) == hipSuccess)
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (march_lights<true, PAIRS>), 256, 0) == hipSuccess)
       n = std::max(1, per_cu * cus / 8);
     else
       n = (int)kLightSlots;
@@ -1447,7 +1610,12 @@ hipError_t launch_march(const MarchDev& m0, const CamDev& cam, const MarchBuf& b
   m.nby = buf.nby;
   m.nbz = buf.nbz;
   const TileMap tm = tile_map(cam);
-  if (!m.brick) {  // build the bricks in the scratch; one extra block balances the bands
+  if (m.pairs) {  // build the plane pairs in the scratch; one extra block balances the bands
+    m.pair = buf.pair;
+    const int plane = (m.nx + 2) * (m.ny + 2);
+    hipLaunchKernelGGL(pairs_balance, dim3((plane + 255) / 256, m.nz / kPairZ + 2), dim3(256), 0, s, m, cam, tm, buf.ctr,
+                       buf.pair);
+  } else if (!m.brick) {  // the bricks, likewise
     m.brick = buf.brick;
     hipLaunchKernelGGL(relayout_balance,
                        dim3((m.nbx + kRelayBricks - 1) / kRelayBricks, (m.nby + kRelayY - 1) / kRelayY, m.nbz + 1),
@@ -1455,7 +1623,10 @@ hipError_t launch_march(const MarchDev& m0, const CamDev& cam, const MarchBuf& b
   } else {
     hipLaunchKernelGGL(march_balance, dim3(1), dim3(kBalanceThreads), 0, s, m, cam, tm, buf.ctr);
   }
-  hipLaunchKernelGGL(march_primary, dim3(8 * tm.per_xcd), dim3(256), 0, s, m, cam, tm, buf, guide);
+  if (m.pairs)
+    hipLaunchKernelGGL(march_primary<true>, dim3(8 * tm.per_xcd), dim3(256), 0, s, m, cam, tm, buf, guide);
+  else
+    hipLaunchKernelGGL(march_primary<false>, dim3(8 * tm.per_xcd), dim3(256), 0, s, m, cam, tm, buf, guide);
   if (m.zorder == kOrderCells) {
     // the scatter with one lane per pixel; the light marches with one
     // workgroup per CU (the planes take most of its LDS)
@@ -1464,14 +1635,18 @@ hipError_t launch_march(const MarchDev& m0, const CamDev& cam, const MarchBuf& b
                        cell_planes_bytes(m.nx, m.ny), s, m, cam, buf);
   } else if (m.zorder) {
     // the blocks resident at once; each loops over units of its XCD's range
-    const int slots = (int)std::min<size_t>((buf.cap + 255) / 256, (size_t)light_blocks_per_xcd());
+    const size_t resident = m.pairs ? light_blocks_per_xcd<true>() : light_blocks_per_xcd<false>();
+    const int slots = (int)std::min<size_t>((buf.cap + 255) / 256, resident);
     hipLaunchKernelGGL(zsort_records, dim3(8 * slots), dim3(256), 0, s, buf);
-    hipLaunchKernelGGL(march_lights<true>, dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
+    if (m.pairs)
+      hipLaunchKernelGGL((march_lights<true, true>), dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
+    else
+      hipLaunchKernelGGL((march_lights<true, false>), dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
   } else {
     // enough workgroups to fill the chip a few times over; each loops over
     // its eighth of the records
     const int slots = (int)std::min<size_t>((buf.cap + 255) / 256, kLightSlots);
-    hipLaunchKernelGGL(march_lights<false>, dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
+    hipLaunchKernelGGL((march_lights<false, false>), dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
   }
   hipLaunchKernelGGL(march_accumulate, dim3((buf.P + 255) / 256), dim3(256), 0, s, m, buf, guide);
   return hipGetLastError();

@@ -32,15 +32,15 @@ static int tiles_per_band(int W, int H) { return (((W + kTile - 1) / kTile) * ((
 // Scratch: [K][P] planes t, A, T_{n-1}, T_top, T_bottom; per-pixel counts; the
 // counter block; 8 band work lists of (pixel, k) with room for every sample
 // of the band's pixels (not in cell order); in the z orders the [K][P]
-// z-bucket plane and the z-ordered list (room for every sample); the bricked
-// grid unless the caller supplies it.
+// z-bucket plane and the z-ordered list (room for every sample); the plane
+// pairs, or the bricked grid unless the caller supplies it.
 size_t march_scratch_bytes(const MarchDev& m, int K, int W, int H) {
   const size_t P = (size_t)W * H, plane = a256(sizeof(float) * (size_t)K * P);
   const size_t cap = (size_t)tiles_per_band(W, H) * kTile * kTile * K;
   return 5 * plane + a256(sizeof(int) * P) + a256(kCounterBytes) +
          (m.zorder != kOrderCells ? a256(8 * cap * sizeof(int2)) : 0) +
          (m.zorder ? a256((size_t)K * P) + a256(sizeof(int2) * (size_t)K * P) : 0) +
-         (m.brick ? 0 : a256(bricks_bytes(m.nx, m.ny, m.nz)));
+         (m.pairs ? a256(pairs_bytes(m.nx, m.ny, m.nz)) : m.brick ? 0 : a256(bricks_bytes(m.nx, m.ny, m.nz)));
 }
 
 // Cell order: the two planes of a cell in LDS, beside the kernel's own
@@ -55,6 +55,22 @@ int march_order(int work_order, int light_set, int nx, int ny, int nz) {
   if (work_order == LNM_ORDER_CELLS) return cells_fit(nx, ny, nz) ? kOrderCells : -1;
   if (bricks_bytes(nx, ny, nz) > kZOrderBytes) return kOrderLayers;
   return light_set == LNM_LIGHTS_TOP_BOTTOM && cells_fit(nx, ny, nz) ? kOrderCells : kOrderBands;
+}
+
+// Plane pairs (z order): a sample is two 16-byte loads (rows j and j + 1 of
+// its cell's pair of planes) instead of a brick's four 8-byte ones, and the
+// gathers cost by the instruction (17 to 38 cycles for 64 lanes, 8 bytes and
+// 16 alike), which bounds the z order's light marches: 1950 -> 1275 us at 256^3
+// / 1024^2, two such marches of a serving batch 919 -> 695 us.  Building them
+// takes what building the bricks takes; where the caller gives bricks, the
+// marches of views from 0.002 pixels per voxel on win it back (256^3: 310
+// against 337 us at 192^2, 266 against 207 at 128^2; 160^3: 84 against 88 at
+// 96^2, 75 against 68 at 64^2).  In cell order, whose light marches read LDS,
+// they gained nothing over the bricks.
+size_t pairs_bytes(int nx, int ny, int nz) { return 2 * sizeof(float) * (size_t)(nx + 2) * (ny + 2) * (nz + 1); }
+bool march_pairs(const MarchDev& m, int W, int H) {
+  if (m.zorder != kOrderLayers || pairs_bytes(m.nx, m.ny, m.nz) > 0xFFFFFFFFull) return false;
+  return !m.brick || (double)W * H >= 0.002 * m.nx * m.ny * m.nz;
 }
 
 MarchBuf march_buffers(void* ws, const MarchDev& m, int K, int W, int H) {
@@ -84,7 +100,8 @@ MarchBuf march_buffers(void* ws, const MarchDev& m, int K, int W, int H) {
     b.srt = reinterpret_cast<int2*>(p);
     p += a256(sizeof(int2) * (size_t)K * P);
   }
-  b.brick = m.brick ? nullptr : reinterpret_cast<float*>(p);
+  b.brick = m.pairs || m.brick ? nullptr : reinterpret_cast<float*>(p);
+  b.pair = m.pairs ? reinterpret_cast<float*>(p) : nullptr;
   b.nbx = bricks_along(m.nx);
   b.nby = bricks_along(m.ny);
   b.nbz = bricks_along(m.nz);
