@@ -125,6 +125,8 @@ static lnm_status march_setup(const lnm_volume* vol, const lnm_camera* cam, cons
   m->zorder = march_order(prm->work_order, prm->light_set, vol->nx, vol->ny, vol->nz);
   if (m->zorder < 0)
     return fail(LNM_ERR_UNSUPPORTED, "params.work_order: a z cell's two grid planes do not fit in LDS");
+  m->zorder2 = m->zorder;
+  m->zorder = march_order_short(prm->work_order, m->zorder, m->h);
   m->brick = vol->bricks;  // NULL: launch_march builds them in its scratch
   m->nbx = m->nby = m->nbz = 0;
   m->pair = nullptr;
@@ -132,12 +134,13 @@ static lnm_status march_setup(const lnm_volume* vol, const lnm_camera* cam, cons
   return LNM_OK;
 }
 
-// Scratch of a march in a workspace of ws_bytes: without the plane pairs when
-// only that fits (the same guiding map from the bricks).
+// Scratch of a march in a workspace of ws_bytes: without the plane pairs, or
+// in the second choice of order, when only that fits (the same guiding map).
 static size_t fit_march(MarchDev* m, int K, int W, int H, size_t ws_bytes) {
   size_t need = march_scratch_bytes(*m, K, W, H);
-  if (ws_bytes < need && m->pairs) {
+  if (ws_bytes < need && (m->pairs || m->zorder != m->zorder2)) {
     m->pairs = 0;
+    m->zorder = m->zorder2;
     need = march_scratch_bytes(*m, K, W, H);
   }
   return need;

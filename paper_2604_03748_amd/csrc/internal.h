@@ -46,6 +46,7 @@ struct MarchDev {
   float wf, wt, wb;  // front and side light intensities
   int light_set;     // lnm_light_set
   int zorder;        // order of the light marches (march_order): bands, z layers or z cells
+  int zorder2;       // the order to take when the workspace has no room for `zorder`
   const float* brick;  // bricked copy of rho (4^3 cells + apron per 128-float slot); caller's or scratch
   int nbx, nby, nbz;   // bricks per axis
   // z order: the march reads plane pairs instead of bricks (march_pairs):
@@ -106,6 +107,8 @@ int march_capacity(const MarchDev& m);
 // fit in LDS, else bands; -1 when LNM_ORDER_CELLS does not fit.
 constexpr int kOrderBands = 0, kOrderLayers = 1, kOrderCells = 2;
 int march_order(int work_order, int light_set, int nx, int ny, int nz);
+// AUTO's z cells become bands when the light marches are short (world step h).
+int march_order_short(int work_order, int order, float h);
 // Whether a march of a W x H view should read plane pairs, and their bytes.
 bool march_pairs(const MarchDev& m, int W, int H);
 size_t pairs_bytes(int nx, int ny, int nz);

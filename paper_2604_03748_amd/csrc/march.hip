@@ -625,6 +625,16 @@ __device__ __forceinline__ int wave_max(int v) {
 // One optical-depth step (tau_n = tau_{n-1} + sigma_n h).
 __device__ __forceinline__ float depth_step(float L, float sig, float h) { return L + sig * h; }
 
+// A value of another lane of the quad by quad permutation (one lane operation,
+// no trip through LDS): lane s - 1's (lane 0: its own), lane 3's, lane s ^ 1's
+// and s ^ 2's.
+template <int CTRL>
+__device__ __forceinline__ int quad_perm(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+__device__ __forceinline__ float quad_prev(float v) { return __int_as_float(quad_perm<0x90>(__float_as_int(v))); }
+__device__ __forceinline__ float quad_last(float v) { return __int_as_float(quad_perm<0xff>(__float_as_int(v))); }
+
 // Primary march of tile `tile` (band order) of band `band`, whose work list
 // starts at `list`, with four lanes per pixel (see below); zh: the block's
 // z-bucket counts, agg: 5 ints of LDS for the block's append.  Every thread
@@ -683,10 +693,10 @@ __device__ __forceinline__ void primary_tile(const MarchDev& m, const CamDev& c,
     float x = s == 0 ? depth_step(tau, sig, h) : 0.0f;
 #pragma unroll
     for (int r = 1; r < 4; ++r) {
-      const float v = __shfl_up(x, 1, 4);
+      const float v = quad_prev(x);
       if (s == r) x = depth_step(v, sig, h);
     }
-    float before = __shfl_up(x, 1, 4);
+    float before = quad_prev(x);
     if (s == 0) before = tau;
     const bool active = valid && before <= m.tau_max;
     const float alpha = riemann ? sig * h : -expm1f(-sig * h);
@@ -708,15 +718,15 @@ __device__ __forceinline__ void primary_tile(const MarchDev& m, const CamDev& c,
     if (active && dn == 0 && sig > m.depth_tau) dn = n;
     k = min(k + __popc(quad), buf.K);
     const unsigned over = (unsigned)(__ballot(active && x > m.tau_max) >> qbase) & 0xfu;
-    tau = __shfl(x, 3, 4);
+    tau = quad_last(x);
     term = over != 0u;
   }
   // quad results: records, depth, transmittance
   const int cnt = k;
   const int big = 0x7fffffff;
   int dmin = dn ? dn : big;
-  dmin = min(dmin, __shfl_xor(dmin, 1, 4));
-  dmin = min(dmin, __shfl_xor(dmin, 2, 4));
+  dmin = min(dmin, quad_perm<0xb1>(dmin));
+  dmin = min(dmin, quad_perm<0x4e>(dmin));
   if (inside && s == 0) {
     buf.cnt[pix] = cnt;
     float* g = guide + 3 * (size_t)pix;

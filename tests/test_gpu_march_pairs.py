@@ -50,3 +50,23 @@ def test_pairs_equal_bricks(shape, proj, eye, light_set):
         run(big - pair_b - 256, bricks)
     bands = ctx.march(vol, 8.0, cam, lnm.make_params(0.7, seed=3, light_set=light_set, work_order=lnm.ORDER_BANDS))
     assert torch.equal(pairs, bands)
+
+
+def test_short_marches_take_bands():
+    """Automatic order at 8 steps per axis: the cells' and the bands' map, also
+    in a workspace of the cells' size only."""
+    import torch
+    from paper_2604_03748_amd import lnm
+
+    ctx = lnm.Context(0)
+    vol = to_dev(np.random.default_rng(4).random((16, 16, 16), dtype=np.float32) * 1.5)
+    cam = Camera(PERSPECTIVE, (2.5, 0.7, 0.4), width=65, height=41)
+    out = {}
+    for order in (lnm.ORDER_AUTO, lnm.ORDER_CELLS, lnm.ORDER_BANDS):
+        prm = lnm.make_params(2.0, seed=3, work_order=order)
+        out[order] = (ctx.march(vol, 8.0, cam, prm).clone(), ctx.march_workspace_bytes(vol, 8.0, cam, prm))
+    auto, n_auto = out[lnm.ORDER_AUTO]
+    assert n_auto == out[lnm.ORDER_BANDS][1]
+    assert torch.equal(auto, out[lnm.ORDER_CELLS][0]) and torch.equal(auto, out[lnm.ORDER_BANDS][0])
+    ws = torch.empty(out[lnm.ORDER_CELLS][1], dtype=torch.uint8, device="cuda")
+    assert torch.equal(auto, ctx.march(vol, 8.0, cam, lnm.make_params(2.0, seed=3), workspace=ws))
