@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "liblnm.so")
 BUILD_DIR = os.path.join(PKG, "_build")
-SOURCES = ["api.hip", "march.hip", "conv.hip", "conv_split.hip", "conv_bf16.hip", "conv_fp8.hip", "train.hip", "train_api.hip", "shadow.hip",
+SOURCES = ["api.hip", "march.hip", "conv.hip", "conv_split.hip", "wgrad.hip", "conv_bf16.hip", "conv_fp8.hip", "train.hip", "train_api.hip", "shadow.hip",
            "adapters.hip", "adapters_train.hip", "frame_static.hip", "plan.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -379,205 +379,6 @@ __global__ __launch_bounds__(256) void composite_batch_kernel(CompositeBatchArgs
   shade_lights(a.l, a.rgb, a.light_lo[b], a.light_lo[b + 1], a.guide, a.rgba, (size_t)p, L);
 }
 
-// Weight gradient of a 3x3 layer: dW[o][c][tap] = sum_p E[p][o] X[p + tap][c]
-// as an MFMA GEMM with M = output channels, N = input channels, K = pixels.
-// A workgroup sums 16 WM output x 16 WN input channels x 9 taps over a group
-// of 8 x 16 pixel tiles: its four wavefronts take the WM x WN channel blocks
-// and, where that leaves wavefronts over, WK shares of each tile's rows
-// (added in order through LDS at the end), so a group writes one partial sum
-// per weight.  X is gathered exactly as the forward pass reads it (pooled /
-// upsampled-concatenated inputs stay virtual).  The next tile's loads are in
-// registers while the matrix cores work on the current one; a lane walks a
-// tile column, so each row of X is read from LDS once for its three taps.
-// The workgroups of the first input-channel block also sum E itself, the
-// bias gradient.
-//
-// Bound by the fp32 matrix rate.  At 8 x 256^2 on the 4-level base-32
-// network all layers' sums and reductions take 1804 us against
-// 9641 us with one partial per wavefront summed by one lane per weight and
-// a separate pass for the bias (5426 of them that pass, 1643 the sums).
-constexpr int kWTH = 8, kWTilePix = kWTH * kTW, kWHaloPix = (kWTH + 2) * kHW;
-
-// LDS floats per pixel of a 16- or 32-channel tile: rows 16-byte aligned, the
-// four pixels that a wavefront reads together on distinct bank halves
-constexpr int wgrad_pitch(int channels) { return channels == 32 ? 40 : 24; }
-
-template <int MODE, int WM, int WN>
-__global__ __launch_bounds__(256, 2) void wgrad3x3_f32(WgradArgs a) {
-  constexpr int WK = 4 / (WM * WN), BM = 16 * WM, BC = 16 * WN;
-  constexpr int PE = wgrad_pitch(BM), PX = wgrad_pitch(BC);
-  constexpr int QE = BM / 4, QX = BC / 4;  // 16-byte groups per pixel
-  constexpr int RE = kWTilePix * QE / 256, RX = (kWHaloPix * QX + 255) / 256;
-  __shared__ __attribute__((aligned(16))) float smem[kWTilePix * PE + kWHaloPix * PX];
-  static_assert((WK - 1) * WM * WN * 9 * 256 <= kWTilePix * PE + kWHaloPix * PX, "row shares must fit in LDS");
-  float* s_e = smem;
-  float* s_x = smem + kWTilePix * PE;
-  const ConvArgs& x = a.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, li = lane & 15;
-  const int wm = wave % WM, wn = (wave / WM) % WN, wk = wave / (WM * WN);
-  const int tiles_x = (x.W + kTW - 1) / kTW, tiles_y = (x.H + kWTH - 1) / kWTH;
-  const int n_tiles = x.B * tiles_x * tiles_y;
-  const int o0 = blockIdx.y * BM, c0 = blockIdx.z * BC;
-
-  Halo<MODE> rx[RX];
-  f4 re[RE];
-  unsigned ok_e = 0, ok_x = 0;
-  auto fetch = [&](int t) {
-    const int b = t / (tiles_x * tiles_y), r = t - b * tiles_x * tiles_y;
-    const int y0 = (r / tiles_x) * kWTH, x0 = (r - (r / tiles_x) * tiles_x) * kTW;
-    ok_e = ok_x = 0;
-#pragma unroll
-    for (int q = 0; q < RE; ++q) {
-      const int p = (tid + 256 * q) / QE, o = o0 + 4 * (tid % QE);
-      const int y = y0 + p / kTW, xx = x0 + p % kTW;
-      ok_e |= (unsigned)(y < x.H && xx < x.W && o < a.co) << q;
-      re[q] = *reinterpret_cast<const f4*>(
-          a.e + ((size_t)(b * x.H + min(y, x.H - 1)) * x.W + min(xx, x.W - 1)) * a.co + min(o, a.co - 4));
-    }
-#pragma unroll
-    for (int q = 0; q < RX; ++q) {
-      const int e = min(tid + 256 * q, kWHaloPix * QX - 1), p = e / QX, c = c0 + 4 * (e % QX);
-      const int y = y0 + p / kHW - 1, xx = x0 + p % kHW - 1;
-      ok_x |= (unsigned)(y >= 0 && y < x.H && xx >= 0 && xx < x.W && c < a.ci) << q;
-      rx[q] = halo_load<MODE>(x, b, min(max(y, 0), x.H - 1), min(max(xx, 0), x.W - 1), c < a.ci ? c : 0);
-    }
-  };
-  const bool with_bias = blockIdx.z == 0;
-  f4 bsum = f4{0.f, 0.f, 0.f, 0.f};
-  auto commit = [&]() {
-#pragma unroll
-    for (int q = 0; q < RE; ++q) {
-      const f4 v = (ok_e >> q) & 1u ? re[q] : f4{0.f, 0.f, 0.f, 0.f};
-      bsum += v;
-      *reinterpret_cast<f4*>(&s_e[((tid + 256 * q) / QE) * PE + 4 * (tid % QE)]) = v;
-    }
-#pragma unroll
-    for (int q = 0; q < RX; ++q) {
-      const int e = tid + 256 * q;
-      if (e < kWHaloPix * QX)
-        *reinterpret_cast<f4*>(&s_x[(e / QX) * PX + 4 * (e % QX)]) = halo_value<MODE>(rx[q], (ok_x >> q) & 1u);
-    }
-  };
-
-  f4 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-  const int t_end = min(n_tiles, (int)(blockIdx.x + 1) * a.tiles_per_group);
-  int t = blockIdx.x * a.tiles_per_group;
-  if (t < t_end) fetch(t);
-  for (; t < t_end; ++t) {
-    commit();
-    __syncthreads();
-    if (t + 1 < t_end) fetch(t + 1);
-    constexpr int NR = kWTH / WK;
-    const int r0 = wk * NR;
-#pragma unroll 1
-    for (int cg = 0; cg < kTW / 4; ++cg) {
-      const float* pe = s_e + (r0 * kTW + 4 * cg + g) * PE + 16 * wm + li;
-      const float* px = s_x + (r0 * kHW + 4 * cg + g) * PX + 16 * wn + li;
-      float xr[3][3];
-#pragma unroll
-      for (int dy = 0; dy < 2; ++dy)
-#pragma unroll
-        for (int dx = 0; dx < 3; ++dx) xr[dy][dx] = px[(dy * kHW + dx) * PX];
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-#pragma unroll
-        for (int dx = 0; dx < 3; ++dx) xr[(r + 2) % 3][dx] = px[((r + 2) * kHW + dx) * PX];
-        const float av = pe[r * kTW * PE];
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap)
-          acc[tap] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, xr[(r + tap / 3) % 3][tap % 3], acc[tap], 0, 0, 0);
-      }
-    }
-    __syncthreads();
-  }
-  if constexpr (WK > 1) {  // the row shares of each channel block, added in order
-    f4* sh = reinterpret_cast<f4*>(smem);
-    if (wk > 0) {
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap) sh[((wave - WM * WN) * 9 + tap) * 64 + lane] = acc[tap];
-    }
-    __syncthreads();
-    if (wk == 0) {
-#pragma unroll
-      for (int k = 1; k < WK; ++k)
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap) acc[tap] += sh[((wave + (k - 1) * WM * WN) * 9 + tap) * 64 + lane];
-    }
-  }
-  if (wk == 0) {
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int o = o0 + 16 * wm + 4 * g + rr, c = c0 + 16 * wn + li;
-        a.partial[(((size_t)blockIdx.x * a.co_pad + o) * 9 + tap) * a.ci_pad + c] = acc[tap][rr];
-      }
-  }
-  if (with_bias) {  // lanes tid % QE hold one channel quad each: added in lane order
-    __syncthreads();
-    f4* sh = reinterpret_cast<f4*>(smem);
-    sh[tid] = bsum;
-    __syncthreads();
-    if (tid < BM) {
-      float v = 0.0f;
-      for (int k = 0; k < 256 / QE; ++k) v += sh[k * QE + tid / 4][tid % 4];
-      a.bias_partial[(size_t)blockIdx.x * a.co_pad + o0 + tid] = v;
-    }
-  }
-}
-
-// Finish a layer's weight and bias gradients: each sum over the groups'
-// partials by eight lanes (every eighth group each, then added in order), 32
-// neighbouring sums per block, so that layers with few weights and many
-// groups still fill the chip.
-__global__ __launch_bounds__(256) void wgrad_reduce(WgradArgs a, int groups, int w_blocks) {
-  __shared__ float sh[8][32];
-  const int el = threadIdx.x & 31, rl = threadIdx.x >> 5;
-  const bool bias = (int)blockIdx.x >= w_blocks;
-  const size_t n = bias ? (size_t)a.co_pad : (size_t)a.co_pad * 9 * a.ci_pad;
-  const size_t e = (size_t)(bias ? blockIdx.x - w_blocks : blockIdx.x) * 32 + el;
-  const float* src = (bias ? a.bias_partial : a.partial) + e;
-  float s = 0.0f;
-  if (e < n) {
-    int k = rl;
-    for (; k + 24 < groups; k += 32) {
-      float v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = src[(size_t)(k + 8 * u) * n];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) s += v[u];
-    }
-    for (; k < groups; k += 8) s += src[(size_t)k * n];
-  }
-  sh[rl][el] = s;
-  __syncthreads();
-  if (rl || e >= n) return;
-#pragma unroll
-  for (int k = 1; k < 8; ++k) s += sh[k][el];
-  if (bias) {
-    if ((int)e < a.co) a.grad_b[e] = s;
-    return;
-  }
-  const int c = (int)(e % a.ci_pad), tap = (int)((e / a.ci_pad) % 9), o = (int)(e / ((size_t)9 * a.ci_pad));
-  if (o < a.co && c < a.ci) a.grad_w[((size_t)o * a.ci + c) * 9 + tap] = s;
-}
-
-template <int MODE>
-hipError_t launch_wgrad_mode(const WgradArgs& a, const WgradTiling& t, hipStream_t s) {
-  const dim3 grid(t.groups, t.co_pad / (16 * t.wm), t.ci_pad / (16 * t.wn));
-  if (t.wm == 2 && t.wn == 2)
-    hipLaunchKernelGGL((wgrad3x3_f32<MODE, 2, 2>), grid, dim3(256), 0, s, a);
-  else if (t.wm == 2)
-    hipLaunchKernelGGL((wgrad3x3_f32<MODE, 2, 1>), grid, dim3(256), 0, s, a);
-  else if (t.wn == 2)
-    hipLaunchKernelGGL((wgrad3x3_f32<MODE, 1, 2>), grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((wgrad3x3_f32<MODE, 1, 1>), grid, dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
 template <int CK, int MODE, int TH>
 hipError_t launch_th(const ConvArgs& a, hipStream_t s, const HeadFuse* head) {
   dim3 grid((a.W + kTW - 1) / kTW, ((a.H + TH - 1) / TH) * a.B, a.n_tiles * a.splits);
@@ -626,27 +427,6 @@ hipError_t launch_splitk_reduce(const ConvArgs& a, int out_type, hipStream_t s) 
     case 16: hipLaunchKernelGGL(splitk_reduce<16>, grid, dim3(256), 0, s, a, out_type, total4); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_wgrad3x3(int mode, const WgradArgs& a0, int* n_partials, hipStream_t s) {
-  WgradArgs a = a0;
-  const WgradTiling t = wgrad_tiling(a.co, a.ci, a.x.B, a.x.H, a.x.W);
-  a.co_pad = t.co_pad;
-  a.ci_pad = t.ci_pad;
-  a.tiles_per_group = t.tiles_per_group;
-  *n_partials = t.groups;
-  hipError_t e;
-  switch (mode) {
-    case G_GUIDE: e = launch_wgrad_mode<G_GUIDE>(a, t, s); break;
-    case G_PLAIN: e = launch_wgrad_mode<G_PLAIN>(a, t, s); break;
-    case G_POOL: e = launch_wgrad_mode<G_POOL>(a, t, s); break;
-    case G_CONCAT_UP: e = launch_wgrad_mode<G_CONCAT_UP>(a, t, s); break;
-    default: return hipErrorInvalidValue;
-  }
-  if (e != hipSuccess) return e;
-  const unsigned w_blocks = (unsigned)(((size_t)t.co_pad * 9 * t.ci_pad + 31) / 32), b_blocks = (t.co_pad + 31) / 32;
-  hipLaunchKernelGGL(wgrad_reduce, dim3(w_blocks + b_blocks), dim3(256), 0, s, a, t.groups, (int)w_blocks);
   return hipGetLastError();
 }
 

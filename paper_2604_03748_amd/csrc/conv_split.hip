@@ -12,9 +12,9 @@
 // than the fp32 instruction's (lightmaps of 8 x 256^2, 4 levels, base 32:
 // 2.5e-7 against 6.8e-7).  Six bf16 products take 96 cycles per 16 x 16 x 32
 // block against 256 for fp32's.  Measured on that network: inference 1805 ->
-// 1053 us (161 TFLOP/s of fp32 products), one 256^2 frame 355 -> 317 us; the
+// 1023 us (166 TFLOP/s of fp32 products), one 256^2 frame 355 -> 312 us; the
 // data gradients of a training batch, with the masking, pooling and
-// concatenation passes that they now carry, 2140 -> 1100 us.
+// concatenation passes that they now carry, 2140 -> 1065 us.
 //
 // Same tiles as the fp32-instruction kernel: a workgroup of four wavefronts
 // computes a 4 MF x 16 pixel tile x 32 output channels; per 16-channel input
@@ -32,67 +32,19 @@
 #include "halo_f32.h"
 #include "head.h"
 #include "internal.h"
+#include "split_bf16.h"
 
 namespace lnm {
 namespace {
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 
 constexpr int kCh = 16;     // input channels per chunk
 constexpr int kRow = 56;    // bf16 per LDS row: 3 pieces x 16 channels, padded to 112 bytes
 constexpr int kSteps = 5;   // K = 32 steps per chunk: taps (0, 1), (2, 3), (4, 5), (6, 7), (8, none)
 
-__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{a, b}, bf16x2));
-}
-__device__ __forceinline__ float bf_lo(uint32_t p) { return __uint_as_float(p << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
-
-struct Pieces {
-  u2 hi, mid, lo;  // four bf16 each
-};
-
-// Values from kOver on round to infinity in bf16.  The general form (SAFE)
-// takes them too: a finite one keeps its leading bits as hi (truncated, so
-// the remainder is exact as well); an infinity goes to lo alone, which meets
-// only the other operand's hi, so its products have the signs that fp32's
-// have.  (A NaN makes NaN of every product either way.)
-constexpr float kOver = 0x1.ffp127f;
-__device__ __forceinline__ float max_abs(float m, f4 v) {
-  return fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w)));
-}
-
-template <bool SAFE>
-__device__ __forceinline__ Pieces split(f4 v) {
-  Pieces p;
-  f4 h = v, m;
-  if constexpr (SAFE) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (fabsf(v[e]) >= kOver) h[e] = __uint_as_float(__float_as_uint(v[e]) & 0xffff0000u);
-      if (fabsf(v[e]) == INFINITY) h[e] = 0.0f;
-    }
-  }
-  p.hi = u2{pk_bf16(h.x, h.y), pk_bf16(h.z, h.w)};
-  f4 r = f4{v.x - bf_lo(p.hi.x), v.y - bf_hi(p.hi.x), v.z - bf_lo(p.hi.y), v.w - bf_hi(p.hi.y)};
-  m = r;
-  if constexpr (SAFE) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (fabsf(v[e]) == INFINITY) m[e] = 0.0f;
-  }
-  p.mid = u2{pk_bf16(m.x, m.y), pk_bf16(m.z, m.w)};
-  r = f4{r.x - bf_lo(p.mid.x), r.y - bf_hi(p.mid.x), r.z - bf_lo(p.mid.y), r.w - bf_hi(p.mid.y)};
-  p.lo = u2{pk_bf16(r.x, r.y), pk_bf16(r.z, r.w)};
-  return p;
-}
 // channels [c, c + 4) of an LDS row
 template <bool SAFE>
-__device__ __forceinline__ void store_row(uint16_t* row, int c, f4 v) {
-  const Pieces p = split<SAFE>(v);
+__device__ __forceinline__ void store_row(uint16_t* row, int c, f4 v, float& over) {
+  const Pieces p = split<SAFE>(v, over);
   *reinterpret_cast<u2*>(row + c) = p.hi;
   *reinterpret_cast<u2*>(row + kCh + c) = p.mid;
   *reinterpret_cast<u2*>(row + 2 * kCh + c) = p.lo;
@@ -214,12 +166,12 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
     if constexpr (MODE == G_FIRST) first_layer(ch);
   };
   auto commit = [&]() {
+    float over = 0.0f;
     auto put = [&](auto safe, int q, uint16_t* rows, f4 v) {
-      store_row<decltype(safe)::value>(rows + (q / (kCh / 4)) * kRow, 4 * (q % (kCh / 4)), v);
+      store_row<decltype(safe)::value>(rows + (q / (kCh / 4)) * kRow, 4 * (q % (kCh / 4)), v, over);
     };
     constexpr int NV = MODE == G_FIRST ? FT::BPW : RQ;
     f4 v[NV];
-    float m = 0.0f;
 #pragma unroll
     for (int r = 0; r < NV; ++r) {
       if constexpr (MODE == G_FIRST) {
@@ -228,16 +180,13 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
       } else {
         v[r] = halo_value<MODE>(rq[r], (ok >> r) & 1u);
       }
-      m = max_abs(m, v[r]);
     }
-#pragma unroll
-    for (int r = 0; r < RW; ++r) m = max_abs(m, rw[r]);
     auto all = [&](auto safe) {
 #pragma unroll
       for (int r = 0; r < NV; ++r) {
         if constexpr (MODE == G_FIRST) {
           const int q = (wave * FT::BPW + r) * 16 + li;
-          if (q < FT::HP) store_row<decltype(safe)::value>(s_in + q * kRow, 4 * g, v[r]);
+          if (q < FT::HP) store_row<decltype(safe)::value>(s_in + q * kRow, 4 * g, v[r], over);
         } else if (tid + 256 * r < NQ) {
           put(safe, tid + 256 * r, s_in, v[r]);
         }
@@ -246,10 +195,8 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
       for (int r = 0; r < RW; ++r)
         if (tid + 256 * r < NW) put(safe, tid + 256 * r, s_w, rw[r]);
     };
-    if (__builtin_expect(m >= kOver, 0))
-      all(std::true_type{});
-    else
-      all(std::false_type{});
+    all(std::false_type{});
+    if (__builtin_expect(!(over == over), 0)) all(std::true_type{});
   };
 
   // the lane's LDS offsets per step: tap 2 st + g / 2 (none in the last step's
@@ -296,8 +243,6 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
 #pragma unroll
           for (int q = 0; q < 3; ++q)
             xv[mf][q] = *reinterpret_cast<const bf16x8*>(px + (m0 + mf) * kHW * kRow + q * kCh);
-        // pieces (weight, input) of the small products, then the large one
-        constexpr int kTerm[6][2] = {{0, 2}, {2, 0}, {1, 1}, {0, 1}, {1, 0}, {0, 0}};
 #pragma unroll
         for (int t = 0; t < 6; ++t)
 #pragma unroll
@@ -305,7 +250,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
 #pragma unroll
             for (int nf = 0; nf < NF; ++nf) {
               f4& c = t < 5 ? cor[m0 + mf][nf] : acc[m0 + mf][nf];
-              c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[nf][kTerm[t][0]], xv[mf][kTerm[t][1]], c, 0, 0, 0);
+              c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[nf][kSplitTerm[t][0]], xv[mf][kSplitTerm[t][1]], c, 0, 0, 0);
             }
       }
     }

@@ -164,9 +164,10 @@ LayerTiling conv_layer_tiling(const lnm_net_s* net, int i, int B, int h, int w) 
 
 // Weight gradient of a layer: 32 x 32 channels per workgroup (16 where the
 // layer has no more), its pixel tiles cut into as many groups as give the
-// layer about 768 workgroups, three per CU (what their LDS allows at once).
-// More groups cost partial sums written and read back (37 KB per workgroup
-// and way), fewer leave CUs idle.
+// layer at most 512 workgroups, the two per CU that fit at once (with 768 the
+// second round leaves half the CUs idle: 1010 against 910 us for the layers
+// of 8 x 256^2, 4 levels, base 32).  More groups cost partial sums written
+// and read back (37 KB per workgroup and way), fewer leave CUs idle.
 WgradTiling wgrad_tiling(int co, int ci, int B, int h, int w) {
   WgradTiling t;
   t.wm = co > 16 ? 2 : 1;
@@ -175,7 +176,7 @@ WgradTiling wgrad_tiling(int co, int ci, int B, int h, int w) {
   t.co_pad = (co + bm - 1) / bm * bm;
   t.ci_pad = (ci + bc - 1) / bc * bc;
   const int tiles = B * ((w + 15) / 16) * ((h + 7) / 8), pairs = (t.co_pad / bm) * (t.ci_pad / bc);
-  const int want = std::max(1, std::min(tiles, 768 / pairs));
+  const int want = std::max(1, std::min(tiles, 512 / pairs));
   t.tiles_per_group = (tiles + want - 1) / want;
   t.groups = (tiles + t.tiles_per_group - 1) / t.tiles_per_group;
   return t;

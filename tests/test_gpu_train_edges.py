@@ -62,3 +62,27 @@ def test_adapter_gradient(ctx, orc, base, B, H, W):
     got = to_host(tr.adapter_grad())
     ref = orc.adapters_loss_grad(params, 2, base, ad, g.astype(np.float64), t.astype(np.float64))[2]
     _check(_adapter_tensors(got, base), _adapter_tensors(ref, base), (base, H, W))
+
+
+def test_activations_past_bf16(ctx, orc):
+    """First-layer outputs from 3e38 to 3.4e38, which the three-piece splits'
+    plain form cannot hold (it rounds the largest to infinity): the second
+    layer's weight gradient, which sums products of them."""
+    from paper_2604_03748_amd import lnm
+
+    base, params = 16, _params(2, 16)
+    parts = _split(params, 2, base)
+    parts["enc0a.w"][:] = 0.0
+    parts["enc0a.w"].reshape(base, 3, 9)[np.arange(base), np.arange(base) % 3, 4] = 3.4e38
+    parts["enc0a.b"][:] = 0.0
+    parts["enc0b.w"][:] = (1.0 + parts["enc0b.w"]) * 1e-36  # outputs near 2e4
+    parts["bot1a.w"][:] *= 1e-4
+    parts["dec0a.w"].reshape(base, 3 * base, 9)[:, :base] *= 1e-4
+    g, t = _batch(1, 24, 40, 7)
+    g[:] = np.random.default_rng(8).choice([0.0, 0.9, 1.0], g.shape)
+    tr = lnm.Trainer(ctx, 2, base, params)
+    _, grad = tr.grad(to_dev(g), to_dev(t))
+    ref = orc.unet_loss_grad(params, 2, base, g.astype(np.float64), t.astype(np.float64))[1]
+    got, ref = (_split(v.astype(np.float64), 2, base)["enc0b.w"] for v in (to_host(grad), ref))
+    assert np.isfinite(got).all() and np.abs(ref).max() > 1e20
+    assert np.linalg.norm(got - ref) <= GRAD_REL * np.linalg.norm(ref)
