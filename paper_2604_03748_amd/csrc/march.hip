@@ -1418,29 +1418,65 @@ __device__ __forceinline__ float ray_value(const MarchDev& m, const GridRay& r, 
   return v;
 }
 
+// Voxels of a reference march's LDS box (8 KB: LDS then admits five
+// wavefronts per SIMD, as many as the registers do).
+constexpr int kRefBox = 2048;
+
+// largest value of the wavefront, in a scalar (DPP: within rows of 16 lanes,
+// then across them; lanes without a source keep their own value)
+__device__ __forceinline__ float wave_max(float v) {
+#define LNM_MAX_STEP(ctrl)                                                                                       \
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), ctrl, 0xf, 0xf, \
+                                                          false)))
+  LNM_MAX_STEP(0x111);  // row_shr 1, 2, 4, 8
+  LNM_MAX_STEP(0x112);
+  LNM_MAX_STEP(0x114);
+  LNM_MAX_STEP(0x118);
+  LNM_MAX_STEP(0x142);  // row_bcast 15, 31
+  LNM_MAX_STEP(0x143);
+#undef LNM_MAX_STEP
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 // Transmittance from x toward l on the linear grid: exp(-h sum_k sigma(x +
 // k h l)) over the points inside the support box, 0 once the optical depth
-// passes tau_max.  Most of a march's points lie in the interior, where all eight
-// corners are grid values: those steps run without border tests, the four
-// corner rows read through one 32-bit offset from four uniform row pointers
-// (28 instead of about 100 lane operations per sample).  The steps up to
-// `kin` are interior: the first and the last of them lie in [0, n - 1) on
-// every axis and the points between move monotonically (a fused multiply-add
-// rounds monotonically), so every index is in the grid.
-__device__ __forceinline__ float reference_transmittance(const MarchDev& m, V3 x, V3 l, float h) {
-  const int kmax = light_steps(m, x, l, h);
+// passes tau_max; 1 (unused) in lanes that do not want it.  Called by whole
+// wavefronts.  Most of a march's points lie in the interior, where all eight
+// corners are grid values: those steps, k0 .. kin, run without border tests.
+// The first and the last of them lie in [0, n - 1) on every axis and the
+// points between move monotonically (a fused multiply-add rounds
+// monotonically), so every index is in the grid.
+//
+// The lanes' marches start a few voxels from one another and run in one
+// direction, so up to 32 steps of all of them stay in a small box of voxels.  It
+// is copied to LDS (a few coalesced loads) and the corners are read there:
+// each sample's four gathers of 64 scattered lanes cost 22 cycles of a CU's
+// address unit apiece and bounded the march (78% busy).  The box is exact, again
+// by monotony: the lowest start's points bound the others' at each step, and
+// the steps' first and last points the ones between.  A box of more than
+// two voxels per sample would cost more loads than the gathers: where eight
+// steps do not fit (pixels of many voxels), the corners are gathered.
+__device__ __forceinline__ float reference_transmittance(const MarchDev& m, bool want, V3 x, V3 l, float h,
+                                                         float* box) {
+  int kmax = want ? light_steps(m, x, l, h) : 0;
   const float scale = m.sigma_scale * h, lim = m.tau_max / scale;
-  const int n[3] = {m.nx, m.ny, m.nz};
+  const int n[3] = {m.nx, m.ny, m.nz}, lane = threadIdx.x;
   const float px[3] = {x.x, x.y, x.z}, dl[3] = {l.x, l.y, l.z};
   GridRay r;
-  float reach = (float)kmax;
-  bool in = true;
+  // interior steps k0 .. kin; the estimates' rounding is put right below
+  float enter = 1.0f, reach = (float)kmax;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
+    const float end = (float)(n[a] - 1);
     r.g[a] = fmaf(px[a], (float)n[a], -0.5f);
     r.dg[a] = dl[a] * h * (float)n[a];
-    in = in && r.g[a] >= 0.0f && r.g[a] < (float)(n[a] - 1);
-    if (r.dg[a] != 0.0f) reach = fminf(reach, ((r.dg[a] > 0.0f ? (float)(n[a] - 1) : 0.0f) - r.g[a]) / r.dg[a]);
+    if (r.dg[a] != 0.0f) {
+      const float inv = __builtin_amdgcn_rcpf(r.dg[a]), t0 = -r.g[a] * inv, t1 = (end - r.g[a]) * inv;
+      enter = fmaxf(enter, fminf(t0, t1));
+      reach = fminf(reach, fmaxf(t0, t1));
+    } else if (!(r.g[a] >= 0.0f && r.g[a] < end)) {
+      reach = 0.0f;
+    }
   }
   auto interior = [&](int k) {
     bool ok = true;
@@ -1451,17 +1487,113 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, V3 x
     }
     return ok;
   };
-  int kin = in && reach >= 1.0f ? (int)reach : 0;
-  while (kin > 0 && !interior(kin)) --kin;  // `reach` is rounded: at most a step or two
-  // the four corner rows' bytes from the point's 32-bit byte offset (a grid
-  // is under 2^32 bytes: its bricks, twice that size, are)
+  int kin = 0, k0 = 1;
+  if (reach >= enter) {
+    kin = (int)reach;
+    k0 = (int)ceilf(enter);
+    while (k0 <= kin && !interior(k0)) ++k0;
+    while (kin >= k0 && !interior(kin)) --kin;
+    if (kin < k0) kin = 0, k0 = 1;
+  }
+  // the starts' range over the lanes with interior steps, and the longest of those
+  float lo0[3], hi0[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    lo0[a] = -wave_max(kin > 0 ? -r.g[a] : -INFINITY);
+    hi0[a] = wave_max(kin > 0 ? r.g[a] : -INFINITY);
+  }
+  const bool index24 = max(max(n[0], n[1]), n[2]) < 1 << 24;  // else without boxes (24-bit products below)
+  const int kend = index24 ? (int)wave_max((float)kin) : 0;
+  float acc = 0.0f;
+  bool over = false;
+  for (int k = 1; k < k0 && !over; ++k) {
+    acc += ray_value(m, r, (float)k);
+    over = acc > lim;
+  }
+  if (over) kin = kmax = 0;
+  int k = 1;
+  while (k <= kend && __any(kin >= k)) {
+    // the box of the next steps, halved until it fits
+    int steps = 32, lo[3], sz[3], vol;
+    for (;; steps >>= 1) {
+      const float ka = (float)k, kb = (float)min(k + steps - 1, kend);
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const float p0 = fminf(fmaf(ka, r.dg[a], lo0[a]), fmaf(kb, r.dg[a], lo0[a]));
+        const float p1 = fmaxf(fmaf(ka, r.dg[a], hi0[a]), fmaf(kb, r.dg[a], hi0[a]));
+        // (lanes past their last interior step lie outside the grid)
+        const int i0 = min(max((int)p0, 0), n[a] - 2), i1 = min(max((int)p1 + 1, 1), n[a] - 1);
+        lo[a] = __builtin_amdgcn_readfirstlane(i0);
+        sz[a] = __builtin_amdgcn_readfirstlane(i1 - i0 + 1);
+      }
+      vol = sz[0] * sz[1] * sz[2];
+      if (vol <= min(kRefBox, 128 * steps) || steps == 8) break;
+    }
+    if (vol > 128 * steps) break;
+    const int sx = sz[0], sxy = sz[0] * sz[1];
+    const float rx = 1.0f / (float)sx, ry = 1.0f / (float)sz[1];
+    const char* src = reinterpret_cast<const char*>(m.rho + ((size_t)lo[2] * m.ny + lo[1]) * m.nx + lo[0]);
+    const uint32_t row4 = 4u * m.nx, plane4 = row4 * (uint32_t)m.ny;  // offsets in the grid are under 2^32 bytes
+    __syncthreads();  // the last box has been read
+    for (int e0 = 0; e0 < vol; e0 += 256) {
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        // (e + 1/2) / s is at least 1/(2 s) from a whole number, e under 2^11: exact
+        const int e = min(e0 + 64 * q + lane, vol - 1);
+        const int row = (int)(((float)e + 0.5f) * rx), z = (int)(((float)row + 0.5f) * ry);
+        const uint32_t at = (uint32_t)z * plane4 + (uint32_t)(row - __umul24(z, sz[1])) * row4 +
+                            4u * (uint32_t)(e - __umul24(row, sx));
+        __builtin_memcpy(&v[q], src + at, sizeof(float));
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) box[e0 + 64 * q + lane] = v[q];  // e0 + 255 < kRefBox, a multiple of 256
+    }
+    __syncthreads();
+    // byte offsets in the box, modulo 2^32
+    const int base4 = 4 * ((lo[2] * sz[1] + lo[1]) * sx + lo[0]);
+    const char* corner = reinterpret_cast<const char*>(box);
+    float top = 0.0f;
+    auto sample = [&](float kk) {
+      const float gx = r.at(0, kk), gy = r.at(1, kk), gz = r.at(2, kk);
+      const int at = __umul24((int)gz, 4 * sxy) + (__umul24((int)gy, 4 * sx) + (4 * (int)gx - base4));
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float* c = reinterpret_cast<const float*>(corner + at + (e & 1 ? 4 * sx : 0) + (e & 2 ? 4 * sxy : 0));
+        v[2 * e] = c[0];
+        v[2 * e + 1] = c[1];
+      }
+      return trilerp(v, __builtin_amdgcn_fractf(gx), __builtin_amdgcn_fractf(gy), __builtin_amdgcn_fractf(gz));
+    };
+    const int last = min(k + steps - 1, kin);
+    int j = max(k, k0);
+    float kk = (float)j;
+    for (; j < last; j += 2, kk += 2.0f) {
+      const float s0 = sample(kk), s1 = sample(kk + 1.0f);
+      acc += s0;
+      top = fmaxf(top, acc);
+      acc += s1;
+      top = fmaxf(top, acc);
+    }
+    if (j == last) {
+      acc += sample(kk);
+      top = fmaxf(top, acc);
+    }
+    k += steps;
+    if (top > lim) {
+      over = true;
+      kin = kmax = 0;
+    }
+  }
+  // the rest, where no box of eight steps fits: the four corner rows read
+  // through one 32-bit byte offset from four uniform row pointers (a grid is
+  // under 2^32 bytes: its bricks, twice that size, are)
   const char* row[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
     row[q] = reinterpret_cast<const char*>(m.rho + (q & 1 ? m.nx : 0) + (q & 2 ? (size_t)m.nx * m.ny : 0));
-  float acc = 0.0f;
-  bool over = false;
-  for (int k = 1; k <= kin && !over; k += 4) {
+  for (k = max(k, k0); k <= kin && !over; k += 4) {
     float f[4][3], v[4][8];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -1493,18 +1625,21 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, V3 x
 // Grid: (tiles of 4 x 2 pixels, 6 axes), one wavefront each, eight lanes per
 // pixel.  Lane s of a pixel takes samples n = s (mod 8) of its ray, the optical
 // depth before each from a scan over the eight lanes, so a wavefront's 64
-// light marches start in a few voxels and run in one direction: their loads
-// share cache lines and their lengths are alike.  A ray in the volume costs
+// light marches start in a few voxels and run in one direction: they share
+// a box in LDS (reference_transmittance) and their lengths are alike.  A ray in the volume costs
 // a thousand times one beside it, so the wavefronts are workgroups of their
 // own (four to a workgroup left CUs with one running wavefront: 18.4 ms), and
 // each tile row starts three columns further along, which spreads the
-// volume's columns over the XCDs.  Bound by the gathers' address processing
-// (22 cache accesses per load).  128^3, 256^2, half-voxel steps: 7.1 ms; 114
-// to 163 ms with one lane per pixel marching the six axes one after the other
-// (one wavefront per SIMD).
+// volume's columns over the XCDs.  128^3, 256^2, half-voxel steps: 2.9 to 3.4
+// ms (by scene), vector instructions 86% busy, two thirds of them the
+// interior samples' 36 each; 5.8 to 7.1 ms with every corner gathered from
+// memory and whole marches from the border in border steps, 114 to 163 ms with
+// one lane per pixel marching the six axes one after the other (one wavefront
+// per SIMD).
 constexpr int kRefTX = 4, kRefTY = 2;
 __global__ __launch_bounds__(64) void reference_kernel(MarchDev m, CamDev c, int srgb, int tiles_x,
                                                         float* __restrict__ lm) {
+  __shared__ float box[kRefBox];
   const int lane = threadIdx.x, s = lane & 7, axis = blockIdx.y;
   const int ty = blockIdx.x / tiles_x, tx = (blockIdx.x - ty * tiles_x + 3 * ty) % tiles_x;
   const int i = tx * kRefTX + ((lane >> 3) & 3), j = ty * kRefTY + (lane >> 5);
@@ -1542,7 +1677,9 @@ __global__ __launch_bounds__(64) void reference_kernel(MarchDev m, CamDev c, int
     before = tau + (s == 0 ? 0.0f : before);
     const bool active = valid && before <= m.tau_max;
     const float A = expf(-before) * -expm1f(-sig * h);
-    if (active && A > 0.0f) acc += A * reference_transmittance(m, x, l, h);
+    const bool want = active && A > 0.0f;
+    const float tr = reference_transmittance(m, want, x, l, h, box);
+    if (want) acc += A * tr;
     const unsigned over = (unsigned)(__ballot(active && tau + run > m.tau_max) >> (lane & ~7)) & 0xffu;
     term = term || over != 0u;
     tau += __shfl(run, 7, 8);

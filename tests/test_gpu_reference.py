@@ -1,6 +1,7 @@
 """Reference lightmaps on grids and views where the march's interior part can
 go wrong (axes of one to three cells, non-cubic grids, rays along an axis,
-views that are no multiple of the pixel tile), against the fp64 oracle at
+views that are no multiple of the pixel tile,
+pixels too wide for its boxes), against the fp64 oracle at
 the bound of the other reference test."""
 import numpy as np
 import pytest
@@ -17,6 +18,8 @@ pytestmark = pytest.mark.gpu
     ((17, 9, 30), ORTHOGRAPHIC, (3.0, 0.5, 0.5), (21, 11), 0.5),
     ((30, 17, 9), PERSPECTIVE, (0.45, 0.5, 0.55), (12, 10), 1.0),  # from inside the volume
     ((8, 8, 1), PERSPECTIVE, (1.5, 2.0, 2.5), (6, 3), 2.0),
+    ((90, 70, 101), PERSPECTIVE, (3.0, 0.7, 0.4), (6, 5), 1.0),  # pixels of many voxels: no box fits
+    ((40, 48, 64), PERSPECTIVE, (2.3, 1.9, 2.1), (30, 22), 0.5),  # boxes of 8 to 32 steps
 ])
 def test_reference_edges(orc, shape, proj, eye, size, step):
     from paper_2604_03748_amd import lnm
