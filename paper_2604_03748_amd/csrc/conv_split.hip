@@ -12,7 +12,7 @@
 // than the fp32 instruction's (lightmaps of 8 x 256^2, 4 levels, base 32:
 // 2.5e-7 against 6.8e-7).  Six bf16 products take 96 cycles per 16 x 16 x 32
 // block against 256 for fp32's.  Measured on that network: inference 1805 ->
-// 1023 us (166 TFLOP/s of fp32 products), one 256^2 frame 355 -> 312 us; the
+// 971 us (175 TFLOP/s of fp32 products), one 256^2 frame 355 -> 296 us; the
 // data gradients of a training batch, with the masking, pooling and
 // concatenation passes that they now carry, 2140 -> 1065 us.
 //
@@ -21,8 +21,10 @@
 // chunk the halo and the 9 x 32 x 16 weight slab are split and staged in LDS
 // (the next chunk's fp32 values in registers meanwhile), and the K = 32
 // steps take two taps x 16 channels.  LDS rows hold a pixel's (or weight
-// row's) three 16-channel pieces in 112 bytes, which puts the 16-byte reads
-// of eight neighbouring rows on distinct banks.  The product is taken
+// row's) three 16-channel pieces in 96 bytes without padding: the 16 lanes
+// that one LDS cycle serves (rows 0-3 and 12-15 of one lane group, 4-11 of
+// the next) then lie on distinct banks.  (Rows padded to 112 bytes looked
+// safer and took two cycles: 1023 -> 971 us for the inference above.)  The product is taken
 // transposed (channels as MFMA rows), so a lane ends with four consecutive
 // channels of one pixel: 16-byte stores, and the gradient's routing (see
 // Route) on whole vectors.
@@ -38,7 +40,7 @@ namespace lnm {
 namespace {
 
 constexpr int kCh = 16;     // input channels per chunk
-constexpr int kRow = 56;    // bf16 per LDS row: 3 pieces x 16 channels, padded to 112 bytes
+constexpr int kRow = 48;    // bf16 per LDS row: 3 pieces x 16 channels
 constexpr int kSteps = 5;   // K = 32 steps per chunk: taps (0, 1), (2, 3), (4, 5), (6, 7), (8, none)
 
 // channels [c, c + 4) of an LDS row
