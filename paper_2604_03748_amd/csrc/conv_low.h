@@ -18,11 +18,10 @@
 //
 // Measured against tiles of at most 8 rows x 64 channels that recomputed
 // their addresses per chunk (9 lane operations per MFMA): 16 x 256^2 on the
-// 4-level base-32 bf16 network 1243 -> 574 us (592 TFLOP/s), the convolutions
-// of a 1024^2 frame on the base-48 network 1680 -> 1020 us, of a 512^2 fp8
-// frame 250 -> 200 us.  The low levels are near their tensors' traffic; the
-// others are bound by LDS reads, which at 4 x 4 blocks per wavefront take as
-// long as the products.
+// 4-level base-32 bf16 network 1243 -> 545 us (624 TFLOP/s), the convolutions
+// of a 1024^2 frame on the base-48 network 1680 -> 970 us, of a 512^2 fp8
+// frame 250 -> 190 us.  The matrix cores are busy for about 40% of the large
+// layers' time, LDS for 20%, vector instructions for 25%.
 //
 // The element type T gives: bytes per element ES, LDS bytes per row of 32
 // channels kRow, the 8-channel group type Group, the MFMA, the maximum of
@@ -55,7 +54,7 @@ __device__ __forceinline__ uint32_t max_i16x2(uint32_t a, uint32_t b) {
 }
 
 struct Bf16 {
-  static constexpr int ES = 2, kRow = 80;
+  static constexpr int ES = 2, kRow = 64;
   typedef u4 Group;
   typedef bf16x8 Frag;
   static __device__ __forceinline__ f4 mfma(Frag w, Frag x, f4 c) {
@@ -74,9 +73,15 @@ struct Bf16 {
   static __device__ __forceinline__ Quad first(const ConvArgs&, f4 v) {
     return u2{pk_bf16(fmaxf(v.x, 0.0f), fmaxf(v.y, 0.0f)), pk_bf16(fmaxf(v.z, 0.0f), fmaxf(v.w, 0.0f))};
   }
-  static __device__ __forceinline__ f4 scaled(const ConvArgs& a, f4 acc, int n) {
-    return acc + *reinterpret_cast<const f4*>(a.bias + n);
+  // epilogue: what four channels' sums need, loaded before any store (a load
+  // after a store would wait for it), and the value
+  struct Scale {
+    f4 bias;
+  };
+  static __device__ __forceinline__ Scale scale(const ConvArgs& a, int n) {
+    return {*reinterpret_cast<const f4*>(a.bias + n)};
   }
+  static __device__ __forceinline__ f4 scaled(const ConvArgs&, f4 acc, const Scale& s) { return acc + s.bias; }
   static __device__ __forceinline__ void store(const ConvArgs& a, size_t at, f4 v) {
     if (a.relu) {
 #pragma unroll
@@ -124,10 +129,15 @@ struct Fp8 {
   }
   typedef uint32_t Quad;
   static __device__ __forceinline__ Quad first(const ConvArgs& a, f4 v) { return relu_e4m3(v, a.w0_out_inv); }
-  static __device__ __forceinline__ f4 scaled(const ConvArgs& a, f4 acc, int n) {
-    const f4 w = *reinterpret_cast<const f4*>(a.w_scale + n), bias = *reinterpret_cast<const f4*>(a.bias + n);
+  struct Scale {
+    f4 w, bias;
+  };
+  static __device__ __forceinline__ Scale scale(const ConvArgs& a, int n) {
+    return {*reinterpret_cast<const f4*>(a.w_scale + n), *reinterpret_cast<const f4*>(a.bias + n)};
+  }
+  static __device__ __forceinline__ f4 scaled(const ConvArgs& a, f4 acc, const Scale& s) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[r] = a.in_scale * w[r] * acc[r] + bias[r];
+    for (int r = 0; r < 4; ++r) acc[r] = a.in_scale * s.w[r] * acc[r] + s.bias[r];
     return acc;
   }
   static __device__ __forceinline__ void store(const ConvArgs& a, size_t at, f4 v) {
@@ -157,6 +167,19 @@ __device__ __forceinline__ void stage_guide_bf16(const ConvArgs& a, int b, int y
   }
 }
 
+// LDS byte of 8-channel group c of a row (a halo pixel or a weight row) with
+// column `col` (the pixel's in the tile, the weight's output channel).  bf16:
+// rows without padding, the groups of every other run of four columns changed
+// over in pairs, so that the 16 lanes which one cycle of a 16-byte read serves
+// (columns 0-3 and 12-15 of one lane group, 4-11 of the next) lie on distinct
+// banks, whichever column they start at; rows padded to 80 bytes, as it was,
+// took two cycles (8.0 instead of 4.8 cycles per LDS instruction in all).  fp8:
+// rows padded to 40 bytes (its 8-byte reads gain nothing from the change-over).
+template <class T>
+__device__ __forceinline__ int lds_at(int row, int col, int c) {
+  return row * T::kRow + 8 * T::ES * (T::ES == 2 ? c ^ (((col >> 2) & 1) << 1) : c);
+}
+
 template <class T, int MODE, int MF, int NF, bool HEAD, bool SEQ>
 __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
   typedef typename T::Group Group;
@@ -165,9 +188,10 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
   constexpr int NQ = (TH + 2) * kHW * 4, RQ = (NQ + 255) / 256;        // 8-channel groups of the halo
   constexpr int WV = kCK * T::ES / 16;                                 // 16-byte vectors per weight row
   constexpr int NW = 9 * BN * WV, RW = (NW + 255) / 256;
+  constexpr int kRow = T::kRow;
   constexpr int kHeadBytes = HEAD ? (TH * kTW * (BN + 1) + 6 * BN) * 4 : 0;
-  constexpr int kWBytes = 9 * BN * T::kRow > kHeadBytes ? 9 * BN * T::kRow : kHeadBytes;
-  __shared__ __attribute__((aligned(16))) uint8_t s_in[(TH + 2) * kHW * T::kRow];
+  constexpr int kWBytes = 9 * BN * kRow > kHeadBytes ? 9 * BN * kRow : kHeadBytes;
+  __shared__ __attribute__((aligned(16))) uint8_t s_in[(TH + 2) * kHW * kRow];
   __shared__ __attribute__((aligned(16))) uint8_t s_w[kWBytes];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -301,7 +325,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
           const bool in = first::halo_inside(a, y0, x0, q);  // zero padding outside the image
 #pragma unroll
           for (int nf = 0; nf < 2; ++nf)
-            *reinterpret_cast<typename T::Quad*>(s_in + q * T::kRow + (nf * 16 + 4 * g) * T::ES) =
+            *reinterpret_cast<typename T::Quad*>(s_in + lds_at<T>(q, q % kHW, 2 * nf + (g >> 1)) + 4 * T::ES * (g & 1)) =
                 in ? fr[bb][nf] : typename T::Quad{};
         }
       }
@@ -315,7 +339,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
         else
           v = rq[r][0];
         if (q < NQ)
-          *reinterpret_cast<Group*>(s_in + (q >> 2) * T::kRow + 8 * T::ES * (q & 3)) =
+          *reinterpret_cast<Group*>(s_in + lds_at<T>(q >> 2, (q >> 2) % kHW, q & 3)) =
               live && ((ok >> r) & 1u) ? v : Group{};
       }
     }
@@ -323,8 +347,8 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
     for (int r = 0; r < RW; ++r) {
       const int q = tid + 256 * r;
       if (q < NW) {
-        uint8_t* d = s_w + (q / WV) * T::kRow + 16 * (q % WV);
-        if constexpr (T::kRow % 16 == 0) {
+        uint8_t* d = s_w + lds_at<T>(q / WV, q / WV, q % WV * (4 / WV));
+        if constexpr (kRow % 16 == 0) {
           *reinterpret_cast<u4*>(d) = rw[r];
         } else {
           *reinterpret_cast<u2*>(d) = u2{rw[r].x, rw[r].y};
@@ -338,8 +362,10 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
     stage_guide_bf16<TH>(a, b, y0, x0, s_g);
     __syncthreads();
   }
-  const uint8_t* px = s_in + (wrow * kHW + li) * T::kRow + 8 * T::ES * g;
-  const uint8_t* pw = s_w + li * T::kRow + 8 * T::ES * g;
+  const uint8_t* px[3];  // by the tap's column
+#pragma unroll
+  for (int dx = 0; dx < 3; ++dx) px[dx] = s_in + lds_at<T>(wrow * kHW + li + dx, li + dx, g);
+  const uint8_t* pw = s_w + lds_at<T>(li, li, g);
   const int sp_lo = SEQ ? 0 : ks, sp_hi = SEQ ? splits : ks + 1;
   const int ch_lo = sp_lo * nchunks / splits, ch_end = sp_hi * nchunks / splits;
   if (ch_lo < ch_end) fetch(ch_lo);
@@ -352,10 +378,10 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
     for (int tap = 0; tap < 9; ++tap) {
       Frag wv[NF], xv[MF];
 #pragma unroll
-      for (int nf = 0; nf < NF; ++nf) wv[nf] = *reinterpret_cast<const Frag*>(pw + (tap * BN + nf * 16) * T::kRow);
+      for (int nf = 0; nf < NF; ++nf) wv[nf] = *reinterpret_cast<const Frag*>(pw + (tap * BN + nf * 16) * kRow);
 #pragma unroll
       for (int mf = 0; mf < MF; ++mf)
-        xv[mf] = *reinterpret_cast<const Frag*>(px + ((mf + tap / 3) * kHW + tap % 3) * T::kRow);
+        xv[mf] = *reinterpret_cast<const Frag*>(px[tap % 3] + (mf + tap / 3) * kHW * kRow);
 #pragma unroll
       for (int mf = 0; mf < MF; ++mf)
 #pragma unroll
@@ -383,6 +409,12 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
       return acc[mf][nf];
   };
 
+  // channels past the last tile (not stored) take any valid ones' scales
+  typename T::Scale sc[NF];
+  if (SEQ || a.splits == 1) {
+#pragma unroll
+    for (int nf = 0; nf < NF; ++nf) sc[nf] = T::scale(a, n0 + nf * 16 < a.co ? n0 + nf * 16 + 4 * g : 0);
+  }
   if constexpr (HEAD) {
     // head epilogue: the activations as they would be stored (bf16) and the
     // head weights in LDS (the weight buffer is free after the last chunk's
@@ -395,7 +427,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
 #pragma unroll
       for (int nf = 0; nf < NF; ++nf) {
         const int n = nf * 16 + 4 * g;
-        const f4 v = T::scaled(a, sum(mf, nf), n);
+        const f4 v = T::scaled(a, sum(mf, nf), sc[nf]);
         float* d = sh + ((wrow + mf) * kTW + li) * (BN + 1) + n;
 #pragma unroll
         for (int r = 0; r < 4; r += 2) {
@@ -410,21 +442,23 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
   }
   const int x = x0 + li;
   if (x >= a.W) return;
+  const size_t at0 = ((size_t)(b * a.H + y0 + wrow) * a.W + x) * a.co + n0 + 4 * g, row = (size_t)a.W * a.co;
+  if (!SEQ && a.splits > 1) {
+    float* to = a.partial + (size_t)ks * a.B * a.H * a.W * a.co + at0;
 #pragma unroll
-  for (int mf = 0; mf < MF; ++mf) {
-    const int y = y0 + wrow + mf;
-    if (y >= a.H) continue;
-    const size_t pix = (size_t)(b * a.H + y) * a.W + x;
+    for (int mf = 0; mf < MF; ++mf)
 #pragma unroll
-    for (int nf = 0; nf < NF; ++nf) {
-      const int n = n0 + nf * 16 + 4 * g;
-      if (n0 + nf * 16 >= a.co) continue;  // the channel count is a multiple of 16
-      if (!SEQ && a.splits > 1)
-        *reinterpret_cast<f4*>(a.partial + ((size_t)ks * a.B * a.H * a.W + pix) * a.co + n) = acc[mf][nf];
-      else
-        T::store(a, pix * a.co + n, T::scaled(a, sum(mf, nf), n));
-    }
+      for (int nf = 0; nf < NF; ++nf)
+        if (y0 + wrow + mf < a.H && n0 + nf * 16 < a.co)
+          *reinterpret_cast<f4*>(to + mf * row + nf * 16) = acc[mf][nf];
+    return;
   }
+#pragma unroll
+  for (int mf = 0; mf < MF; ++mf)
+#pragma unroll
+    for (int nf = 0; nf < NF; ++nf)  // the channel count is a multiple of 16
+      if (y0 + wrow + mf < a.H && n0 + nf * 16 < a.co)
+        T::store(a, at0 + mf * row + nf * 16, T::scaled(a, sum(mf, nf), sc[nf]));
 }
 
 template <class T, int MODE, int MF, int NF, bool SEQ>

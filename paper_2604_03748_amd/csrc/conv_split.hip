@@ -285,6 +285,25 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
   }
 
   const int x = x0 + li;
+  // everything the outputs need is loaded ahead of the stores: a load issued
+  // after a store waits for it
+  f4 bias[ROUTE == R_NONE ? NF : 1];
+  if constexpr (ROUTE == R_NONE) {
+    if (a.splits == 1) {
+#pragma unroll
+      for (int nf = 0; nf < NF; ++nf) bias[nf] = *reinterpret_cast<const f4*>(a.bias + nt * kBN + nf * 16 + 4 * g);
+    }
+  }
+  f4 mask[ROUTE == R_MASK ? MF : 1][ROUTE == R_MASK ? NF : 1];
+  if constexpr (ROUTE == R_MASK) {
+#pragma unroll
+    for (int mf = 0; mf < MF; ++mf)
+#pragma unroll
+      for (int nf = 0; nf < NF; ++nf)
+        mask[mf][nf] = *reinterpret_cast<const f4*>(
+            a.y0 + ((size_t)(b * a.H + min(y0 + wrow + mf, a.H - 1)) * a.W + min(x, a.W - 1)) * a.co +
+            min(nt * kBN + nf * 16, a.co - 16) + 4 * g);
+  }
 #pragma unroll
   for (int mf = 0; mf < MF; ++mf) {
     const int y = y0 + wrow + mf;
@@ -302,7 +321,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
               v, reinterpret_cast<f4*>(a.partial + ((size_t)ks * a.B * a.H * a.W + pix) * a.co + n));
           continue;
         }
-        v += *reinterpret_cast<const f4*>(a.bias + n);
+        v += bias[nf];
         if (a.relu) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
@@ -310,7 +329,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
         __builtin_nontemporal_store(v, reinterpret_cast<f4*>(static_cast<float*>(a.out) + pix * a.co + n));
       } else if constexpr (ROUTE == R_MASK) {
         if (!in) continue;
-        const f4 ym = *reinterpret_cast<const f4*>(a.y0 + pix * a.co + n);
+        const f4 ym = mask[mf][nf];
 #pragma unroll
         for (int r = 0; r < 4; ++r) v[r] = ym[r] > 0.0f ? v[r] : 0.0f;
         *reinterpret_cast<f4*>(a.g0 + pix * a.co + n) = v;
