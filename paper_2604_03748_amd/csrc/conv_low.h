@@ -18,15 +18,17 @@
 //
 // Measured against tiles of at most 8 rows x 64 channels that recomputed
 // their addresses per chunk (9 lane operations per MFMA): 16 x 256^2 on the
-// 4-level base-32 bf16 network 1243 -> 545 us (624 TFLOP/s), the convolutions
-// of a 1024^2 frame on the base-48 network 1680 -> 970 us, of a 512^2 fp8
-// frame 250 -> 190 us.  The matrix cores are busy for about 40% of the large
+// 4-level base-32 bf16 network 1243 -> 519 us (655 TFLOP/s), the convolutions
+// of a 1024^2 frame on the base-48 network 1680 -> 940 us, of a 512^2 fp8
+// frame 250 -> 180 us.  The matrix cores are busy for about 40% of the large
 // layers' time, LDS for 20%, vector instructions for 25%.
 //
 // The element type T gives: bytes per element ES, LDS bytes per row of 32
 // channels kRow, the 8-channel group type Group, the MFMA, the maximum of
 // non-negative groups, and the stored form of four outputs.
 #pragma once
+#include <type_traits>
+
 #include "first_layer.h"
 #include "head.h"
 #include "internal.h"
@@ -53,6 +55,21 @@ __device__ __forceinline__ uint32_t max_i16x2(uint32_t a, uint32_t b) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s2, a), __builtin_bit_cast(s2, b)));
 }
 
+// Lane rows (16 lanes) 0 .. 3 hold a word of quads 0 .. 3 of one 16-channel
+// block in p and of the next block in q.  Afterwards row 0 holds p's quads 0
+// and 1, row 2 its quads 2 and 3, row 1 q's quads 0 and 1, row 3 its quads 2
+// and 3: eight consecutive channels in every lane.
+__device__ __forceinline__ u2 join_quads(uint32_t p, uint32_t q) {
+  const auto r = __builtin_amdgcn_permlane16_swap(p, q, false, false);
+  return u2{r[0], r[1]};
+}
+__device__ __forceinline__ u4 join_quads(u2 p, u2 q) {
+  const u2 x = join_quads(p.x, q.x), y = join_quads(p.y, q.y);
+  return u4{x.x, y.x, x.y, y.y};
+}
+
+// The element type T: T::store(a, each) calls each(a.out, f) with f turning
+// four channels' values into what is stored.
 struct Bf16 {
   static constexpr int ES = 2, kRow = 64;
   typedef u4 Group;
@@ -82,12 +99,15 @@ struct Bf16 {
     return {*reinterpret_cast<const f4*>(a.bias + n)};
   }
   static __device__ __forceinline__ f4 scaled(const ConvArgs&, f4 acc, const Scale& s) { return acc + s.bias; }
-  static __device__ __forceinline__ void store(const ConvArgs& a, size_t at, f4 v) {
-    if (a.relu) {
+  template <class F>
+  static __device__ __forceinline__ void store(const ConvArgs& a, const F& each) {
+    each(static_cast<uint16_t*>(a.out), [&](f4 v) {
+      if (a.relu) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
-    }
-    *reinterpret_cast<u2*>(static_cast<uint16_t*>(a.out) + at) = u2{pk_bf16(v.x, v.y), pk_bf16(v.z, v.w)};
+        for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
+      }
+      return u2{pk_bf16(v.x, v.y), pk_bf16(v.z, v.w)};
+    });
   }
 };
 
@@ -140,14 +160,16 @@ struct Fp8 {
     for (int r = 0; r < 4; ++r) acc[r] = a.in_scale * s.w[r] * acc[r] + s.bias[r];
     return acc;
   }
-  static __device__ __forceinline__ void store(const ConvArgs& a, size_t at, f4 v) {
-    if (a.out_bf16) {  // for a bf16 consumer: unscaled
+  template <class F>
+  static __device__ __forceinline__ void store(const ConvArgs& a, const F& each) {
+    if (a.out_bf16)  // for a bf16 consumer: unscaled
+      each(static_cast<uint16_t*>(a.out), [&](f4 v) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
-      *reinterpret_cast<u2*>(static_cast<uint16_t*>(a.out) + at) = u2{pk_bf16(v.x, v.y), pk_bf16(v.z, v.w)};
-      return;
-    }
-    *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(a.out) + at) = relu_e4m3(v, a.out_inv_scale);
+        for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], 0.0f);
+        return u2{pk_bf16(v.x, v.y), pk_bf16(v.z, v.w)};
+      });
+    else
+      each(static_cast<uint8_t*>(a.out), [&](f4 v) { return relu_e4m3(v, a.out_inv_scale); });
   }
 };
 
@@ -262,7 +284,7 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
   u4 rw[RW];
   const int yb = max(y0 - 1, 0), xb = max(x0 - 1, 0);
   const uint8_t *src0 = nullptr, *src1 = nullptr;
-  size_t e0[MODE == G_FIRST ? 1 : RQ], e1[MODE == G_CONCAT_UP ? RQ : 1];
+  uint32_t e0[MODE == G_FIRST ? 1 : RQ], e1[MODE == G_CONCAT_UP ? RQ : 1];  // in units of 16 channels
   unsigned ok = 0;
   if constexpr (MODE != G_FIRST) {
     constexpr int S = MODE == G_POOL ? 2 : 1;
@@ -277,19 +299,19 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
       const int y = y0 + p / kHW - 1, x = x0 + p % kHW - 1;
       ok |= (unsigned)(y >= 0 && y < a.H && x >= 0 && x < a.W) << r;
       const int yc = min(max(y, 0), a.H - 1), xc = min(max(x, 0), a.W - 1);
-      e0[r] = ((size_t)(S * (yc - yb)) * (S * a.W) + S * (xc - xb)) * a.c0 * T::ES;
+      e0[r] = (uint32_t)(((size_t)(S * (yc - yb)) * (S * a.W) + S * (xc - xb)) * (a.c0 / 16));
       if constexpr (MODE == G_CONCAT_UP)
-        e1[r] = ((size_t)((yc >> 1) - (yb >> 1)) * (a.W >> 1) + (xc >> 1) - (xb >> 1)) * a.c1 * T::ES;
+        e1[r] = (uint32_t)(((size_t)((yc >> 1) - (yb >> 1)) * (a.W >> 1) + (xc >> 1) - (xb >> 1)) * (a.c1 / 16));
     }
   }
   // LDS row (tap, n of BN) <- packed [n / 32][chunk][tap][n % 32][32 channels]
   // (past the last tile: the last tile's rows, whose outputs are not stored)
-  int ew[RW];
+  uint32_t ew[RW];
 #pragma unroll
   for (int r = 0; r < RW; ++r) {
     const int q = min(tid + 256 * r, NW - 1), row = q / WV, tap = row / BN, n = n0 + row - tap * BN;
     const int t = min(n / kBN, a.n_tiles - 1);
-    ew[r] = (t * nchunks * 9 + tap) * kBN * kCK * T::ES + (n % kBN) * kCK * T::ES + 16 * (q % WV);
+    ew[r] = (uint32_t)(t * nchunks * 9 + tap) * kBN * kCK * T::ES + (n % kBN) * kCK * T::ES + 16 * (q % WV);
   }
   bool live = true;  // the lane's channels of the fetched chunk exist
   auto fetch = [&](int ch) {
@@ -301,7 +323,9 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
       const uint8_t* src = up ? src1 + (size_t)(c - a.c0) * T::ES : src0 + (size_t)c * T::ES;
 #pragma unroll
       for (int r = 0; r < RQ; ++r) {
-        const uint8_t* q = src + (MODE == G_CONCAT_UP && up ? e1[MODE == G_CONCAT_UP ? r : 0] : e0[r]);
+        uint32_t at = e0[r];
+        if constexpr (MODE == G_CONCAT_UP) at = up ? uint32_t(e1[r]) : at;
+        const uint8_t* q = src + (size_t)at * (16 * T::ES);
         rq[r][0] = *reinterpret_cast<const Group*>(q);
         if constexpr (MODE == G_POOL) {
           const size_t px = (size_t)a.c0 * T::ES, row = 2 * (size_t)a.W * px;
@@ -453,12 +477,26 @@ __global__ __launch_bounds__(256, 2) void conv3x3_low(ConvArgs a, HeadFuse hf) {
           *reinterpret_cast<f4*>(to + mf * row + nf * 16) = acc[mf][nf];
     return;
   }
+  // two 16-channel blocks' quads joined (see join_quads): half as many stores,
+  // of 64 bytes per pixel instead of 32 (bf16)
+  const size_t at2 = at0 - 4 * g + 16 * (g & 1) + 8 * (g >> 1);
+  T::store(a, [&](auto* out, const auto& quad) __attribute__((always_inline)) {
 #pragma unroll
-  for (int mf = 0; mf < MF; ++mf)
+    for (int mf = 0; mf < MF; ++mf) {
+      if (y0 + wrow + mf >= a.H) break;
 #pragma unroll
-    for (int nf = 0; nf < NF; ++nf)  // the channel count is a multiple of 16
-      if (y0 + wrow + mf < a.H && n0 + nf * 16 < a.co)
-        T::store(a, at0 + mf * row + nf * 16, T::scaled(a, sum(mf, nf), sc[nf]));
+      for (int nf = 0; nf < NF; nf += 2) {  // the channel count is a multiple of 16
+        const auto p = quad(T::scaled(a, sum(mf, nf), sc[nf]));
+        if (nf + 1 < NF && n0 + (nf + 1) * 16 < a.co) {
+          constexpr int last = NF - 1;
+          const auto v = join_quads(p, quad(T::scaled(a, sum(mf, min(nf + 1, last)), sc[min(nf + 1, last)])));
+          *reinterpret_cast<std::remove_const_t<decltype(v)>*>(out + at2 + mf * row + nf * 16) = v;
+        } else if (n0 + nf * 16 < a.co) {
+          *reinterpret_cast<std::remove_const_t<decltype(p)>*>(out + at0 + mf * row + nf * 16) = p;
+        }
+      }
+    }
+  });
 }
 
 template <class T, int MODE, int MF, int NF, bool SEQ>
