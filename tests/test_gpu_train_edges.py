@@ -35,7 +35,7 @@ def _check(got, ref, what):
 
 
 @pytest.mark.parametrize("levels,base,B,H,W", [(2, 48, 1, 10, 34), (2, 80, 1, 6, 18), (2, 16, 3, 18, 50),
-                                               (2, 16, 1, 320, 320)])
+                                               (2, 16, 1, 320, 320), (2, 16, 3, 232, 238)])
 def test_trunk_gradient(ctx, orc, levels, base, B, H, W):
     from paper_2604_03748_amd import lnm
 
