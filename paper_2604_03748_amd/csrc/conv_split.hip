@@ -167,6 +167,9 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
     for (int r = 0; r < RW; ++r) rw[r] = *reinterpret_cast<const f4*>(wsrc + 4 * min(tid + 256 * r, NW - 1));
     if constexpr (MODE == G_FIRST) first_layer(ch);
   };
+  // (Lanes past the end hold the last entry again.  Storing it once more is
+  // cheaper than a branch per entry where the registers let all entries' splits
+  // overlap, up to 8-row tiles.)
   auto commit = [&]() {
     float over = 0.0f;
     auto put = [&](auto safe, int q, uint16_t* rows, f4 v) {
@@ -189,13 +192,13 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
         if constexpr (MODE == G_FIRST) {
           const int q = (wave * FT::BPW + r) * 16 + li;
           if (q < FT::HP) store_row<decltype(safe)::value>(s_in + q * kRow, 4 * g, v[r], over);
-        } else if (tid + 256 * r < NQ) {
-          put(safe, tid + 256 * r, s_in, v[r]);
+        } else {
+          if (MF <= 2 || tid + 256 * r < NQ) put(safe, min(tid + 256 * r, NQ - 1), s_in, v[r]);
         }
       }
 #pragma unroll
       for (int r = 0; r < RW; ++r)
-        if (tid + 256 * r < NW) put(safe, tid + 256 * r, s_w, rw[r]);
+        if (MF <= 2 || tid + 256 * r < NW) put(safe, min(tid + 256 * r, NW - 1), s_w, rw[r]);
     };
     all(std::false_type{});
     if (__builtin_expect(!(over == over), 0)) all(std::true_type{});
@@ -222,11 +225,14 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
     first::stage_guide<TH>(a, b, y0, x0, s_g);
     __syncthreads();
   }
-  if (ch_lo < ch_hi) fetch(ch_lo);
-  for (int ch = ch_lo; ch < ch_hi; ++ch) {
-    commit();
-    __syncthreads();
-    if (ch + 1 < ch_hi) fetch(ch + 1);
+  constexpr int MG = MF < 2 ? MF : 2;  // pixel rows whose products alternate
+  // The staged chunk's products, and the next one's loads.  Each step's
+  // operands are read among the step before's products and the loads issued
+  // among the first steps' in 4-row tiles, whose few wavefronts hide neither
+  // (2040 -> 1290 cycles for 60 products by the reads alone; the
+  // base-16 network's small images 65 -> 62 us, a 256^2 frame 300 -> 294).  Taller tiles gain nothing.
+  auto products = [&](int ch, auto more) __attribute__((always_inline)) {
+    if constexpr (decltype(more)::value) fetch(ch + 1);
 #pragma unroll
     for (int st = 0; st < kSteps; ++st) {
       const uint16_t* pw = (st == kSteps - 1 ? last_w : s_w) + at_w[st];
@@ -236,7 +242,6 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
       for (int nf = 0; nf < NF; ++nf)
 #pragma unroll
         for (int q = 0; q < 3; ++q) wv[nf][q] = *reinterpret_cast<const bf16x8*>(pw + nf * 16 * kRow + q * kCh);
-      constexpr int MG = MF < 2 ? MF : 2;  // pixel rows whose products alternate
 #pragma unroll
       for (int m0 = 0; m0 < MF; m0 += MG) {
         bf16x8 xv[MG][3];
@@ -255,6 +260,35 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
               c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[nf][kSplitTerm[t][0]], xv[mf][kSplitTerm[t][1]], c, 0, 0, 0);
             }
       }
+    }
+    if constexpr (MF == 1) {
+      constexpr int kReads = 3 * (NF + MF), kMul = 6 * NF * MF;
+      constexpr int kLoads = decltype(more)::value ? RW + (MODE == G_FIRST ? 0 : RQ * (MODE == G_POOL ? 4 : 1)) : 0;
+      __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
+#pragma unroll
+      for (int st = 0; st < kSteps; ++st) {
+#pragma unroll
+        for (int k = 0; k < kReads; ++k) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          if (st + 1 < kSteps) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          if (k % 3 == 0 && st * (kReads / 3) + k / 3 < kLoads) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, kMul - kReads, 0);
+      }
+    }
+  };
+  if (ch_lo < ch_hi) fetch(ch_lo);
+  for (int ch = ch_lo; ch < ch_hi; ++ch) {
+    commit();
+    __syncthreads();
+    if constexpr (MF == 1) {
+      if (ch + 1 < ch_hi)
+        products(ch, std::true_type{});
+      else
+        products(ch, std::false_type{});
+    } else {
+      if (ch + 1 < ch_hi) fetch(ch + 1);
+      products(ch, std::false_type{});
     }
     __syncthreads();
   }
