@@ -41,6 +41,8 @@ if ROOT not in sys.path:
 METRIC = "lightmap frames/s at 128³ grid/256² view, FP32 vs BF16; served p50/p99 latency"
 # published dense matrix peaks of MI355X (TFLOP/s) and HBM bandwidth (GB/s)
 PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0, "fp8": 5000.0}
+# fp32 inference takes each product as six bf16 ones (three-piece splits)
+CONV_PEAK_TFLOPS = {**PEAK_TFLOPS, "fp32": round(PEAK_TFLOPS["bf16"] / 6, 1)}
 HBM_PEAK_GBS = 8000.0
 
 
@@ -373,9 +375,9 @@ def precision_report(lnm, ctx, wl, params, dens, weights="He-normal seed 0 (untr
 # the conv kernels, their tiling / split-K choice (conv_layer_tiling in
 # plan.hip) and the head epilogue; the march kernels and their work order
 # and buffers (plan.hip)
-CONV_SOURCES = ("paper_2604_03748_amd/csrc/conv.hip", "paper_2604_03748_amd/csrc/conv_bf16.hip",
-                "paper_2604_03748_amd/csrc/conv_fp8.hip", "paper_2604_03748_amd/csrc/head.h",
-                "paper_2604_03748_amd/csrc/first_layer.h", "paper_2604_03748_amd/csrc/plan.hip")
+CONV_SOURCES = tuple("paper_2604_03748_amd/csrc/" + f for f in (
+    "conv.hip", "conv_split.hip", "split_bf16.h", "halo_f32.h", "conv_bf16.hip", "conv_fp8.hip", "conv_low.h",
+    "head.h", "first_layer.h", "plan.hip"))
 MARCH_SOURCES = ("paper_2604_03748_amd/csrc/march.hip", "paper_2604_03748_amd/csrc/ray.h",
                  "paper_2604_03748_amd/csrc/plan.hip")
 
@@ -510,16 +512,16 @@ def conv_roofline(wl, stage, dtype):
     H, W = wl.camera.height, wl.camera.width
     conv_flops = unet_flops(wl.levels, wl.base, 1, H, W) - 2.0 * H * W * 6 * wl.base  # 3x3 layers only
     # the 3x3 layers' algorithmic FLOPs over their time per frame; the
-    # launches are counted as made (fp32 and bf16 run the first two layers
-    # as one)
+    # launches are counted as made (inference runs the first two layers as one)
     n_conv = stage["conv3x3"]["launches_per_frame"]
     us = stage["conv3x3"]["us_per_frame"] / n_conv
     per_launch = conv_flops / n_conv
     achieved = per_launch / (us * 1e-6) / 1e12
-    kern = {"fp32": "conv3x3_f32 (v_mfma_f32_16x16x4_f32)", "bf16": "conv3x3_bf16 (v_mfma_f32_16x16x32_bf16)",
-            "fp8": "conv3x3_fp8 (v_mfma_f32_16x16x32_fp8_fp8)"}[dtype]
-    return {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_TFLOPS[dtype], "unit": "TFLOP/s",
-            "frac": round(achieved / PEAK_TFLOPS[dtype], 5), "traffic": measured_traffic(dtype), "kernel": kern,
+    kern = {"fp32": "conv3x3_split (six v_mfma_f32_16x16x32_bf16 per product)",
+            "bf16": "conv3x3_low<Bf16> (v_mfma_f32_16x16x32_bf16)",
+            "fp8": "conv3x3_low<Fp8> (v_mfma_f32_16x16x32_fp8_fp8)"}[dtype]
+    return {"bound": "mfma", "achieved": round(achieved, 3), "peak": CONV_PEAK_TFLOPS[dtype], "unit": "TFLOP/s",
+            "frac": round(achieved / CONV_PEAK_TFLOPS[dtype], 5), "traffic": measured_traffic(dtype), "kernel": kern,
             "flops_per_launch": round(per_launch), "us_per_launch": round(us, 3),
             "launches_per_frame": round(n_conv, 3)}
 
