@@ -1531,20 +1531,35 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, bool
     }
     if (vol > 128 * steps) break;
     const int sx = sz[0], sxy = sz[0] * sz[1];
-    const float rx = 1.0f / (float)sx, ry = 1.0f / (float)sz[1];
+    // Lane `lane` copies entries lane, lane + 64, ...: the first one's place by
+    // division ((e + 1/2) / s is at least 1/(2 s) from a whole number, e under
+    // 2^6: exact), the next ones' by steps of 64 entries with carries, in the
+    // box and in the grid (whose byte offsets are under 2^32).
     const char* src = reinterpret_cast<const char*>(m.rho + ((size_t)lo[2] * m.ny + lo[1]) * m.nx + lo[0]);
-    const uint32_t row4 = 4u * m.nx, plane4 = row4 * (uint32_t)m.ny;  // offsets in the grid are under 2^32 bytes
+    const uint32_t row4 = 4u * m.nx, plane4 = row4 * (uint32_t)m.ny;
+    const float rx = 1.0f / (float)sx, ry = 1.0f / (float)sz[1];
+    const int yl = (int)(((float)lane + 0.5f) * rx), zl = (int)(((float)yl + 0.5f) * ry);
+    uint32_t ex = lane - yl * sx, ey = yl - zl * sz[1];
+    uint32_t at = (uint32_t)zl * plane4 + ey * row4 + 4u * ex;
+    const int ys = __builtin_amdgcn_readfirstlane((int)(64.5f * rx));  // rows in 64 entries
+    const int zs = __builtin_amdgcn_readfirstlane((int)(((float)ys + 0.5f) * ry));
+    const uint32_t dx = 64 - ys * sx, dy = ys - zs * sz[1];
+    const uint32_t d4 = (uint32_t)zs * plane4 + dy * row4 + 4u * dx;
+    const uint32_t carry_x = row4 - 4u * sx, carry_y = plane4 - row4 * (uint32_t)sz[1];
     __syncthreads();  // the last box has been read
     for (int e0 = 0; e0 < vol; e0 += 256) {
       float v[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        // (e + 1/2) / s is at least 1/(2 s) from a whole number, e under 2^11: exact
-        const int e = min(e0 + 64 * q + lane, vol - 1);
-        const int row = (int)(((float)e + 0.5f) * rx), z = (int)(((float)row + 0.5f) * ry);
-        const uint32_t at = (uint32_t)z * plane4 + (uint32_t)(row - __umul24(z, sz[1])) * row4 +
-                            4u * (uint32_t)(e - __umul24(row, sx));
-        __builtin_memcpy(&v[q], src + at, sizeof(float));
+        const uint32_t ok = e0 + 64 * q + lane < vol ? at : 0u;  // past the end: the first entry
+        __builtin_memcpy(&v[q], src + ok, sizeof(float));
+        ex += dx;
+        const bool cx = ex >= (uint32_t)sx;
+        ex -= cx ? sx : 0;
+        ey += dy + (cx ? 1u : 0u);
+        const bool cy = ey >= (uint32_t)sz[1];
+        ey -= cy ? sz[1] : 0;
+        at += d4 + (cx ? carry_x : 0u) + (cy ? carry_y : 0u);
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) box[e0 + 64 * q + lane] = v[q];  // e0 + 255 < kRefBox, a multiple of 256
@@ -1564,7 +1579,10 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, bool
         v[2 * e] = c[0];
         v[2 * e + 1] = c[1];
       }
-      return trilerp(v, __builtin_amdgcn_fractf(gx), __builtin_amdgcn_fractf(gy), __builtin_amdgcn_fractf(gz));
+      const float fx = __builtin_amdgcn_fractf(gx), fy = __builtin_amdgcn_fractf(gy), fz = __builtin_amdgcn_fractf(gz);
+      auto lerp = [](float p, float q, float f) { return fmaf(f, q - p, p); };
+      return lerp(lerp(lerp(v[0], v[1], fx), lerp(v[2], v[3], fx), fy),
+                  lerp(lerp(v[4], v[5], fx), lerp(v[6], v[7], fx), fy), fz);
     };
     const int last = min(k + steps - 1, kin);
     int j = max(k, k0);
@@ -1630,9 +1648,9 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, bool
 // a thousand times one beside it, so the wavefronts are workgroups of their
 // own (four to a workgroup left CUs with one running wavefront: 18.4 ms), and
 // each tile row starts three columns further along, which spreads the
-// volume's columns over the XCDs.  128^3, 256^2, half-voxel steps: 2.9 to 3.4
-// ms (by scene), vector instructions 86% busy, two thirds of them the
-// interior samples' 36 each; 5.8 to 7.1 ms with every corner gathered from
+// volume's columns over the XCDs.  128^3, 256^2, half-voxel steps: 2.9 to 3.3
+// ms (by scene), vector instructions 86% busy, most of them the interior
+// samples' 33 each; 5.8 to 7.1 ms with every corner gathered from
 // memory and whole marches from the border in border steps, 114 to 163 ms with
 // one lane per pixel marching the six axes one after the other (one wavefront
 // per SIMD).
