@@ -808,21 +808,22 @@ __device__ __forceinline__ int tile_cost(const MarchDev& m, const CamDev& c, con
 // Zero the band counters and cut the band order of tiles into 8 ranges of
 // about equal estimated cost (start[0..8] after the counters).  The smoke
 // often covers a small part of the screen; equal screen bands would leave
-// most XCDs idle.  One workgroup of 256 lanes: per-lane sums over contiguous
-// tile runs, an LDS scan, then each tile goes to range floor(8 (prefix +
-// cost / 2) / total); all sums are integers, so the ranges are exact and
-// contiguous.  The first kCostCache tile costs are kept in LDS for the
-// second pass.
-constexpr int kBalanceThreads = 256, kCostCache = 2048;
+// most XCDs idle.  One workgroup of 256 lanes, each taking a contiguous part
+// of the order in at most kBalanceRuns runs of tiles, a run priced by its
+// middle tile: sums over the runs, an LDS scan, then each run goes to range
+// floor(8 (prefix + cost / 2) / total); all sums are integers, so the ranges
+// are exact and contiguous.  The workgroup runs beside the grid's copy and
+// must not outlast it: with every tile priced (and a 64-bit division each) it
+// took 30 us of a 512^2 march where the copy of a 128^3 grid takes 9.
+constexpr int kBalanceThreads = 256, kBalanceRuns = 4;
 struct BalanceLds {
   long long scan[2][kBalanceThreads];
-  int cost[kCostCache];
   int first[8];
 };
 __device__ void balance_tiles(const MarchDev& m, const CamDev& c, const TileMap& tm, int* __restrict__ ctr,
                               BalanceLds& sh) {
   const int tid = threadIdx.x, ntiles = tm.tiles_x * tm.tiles_y;
-  const int per = (ntiles + kBalanceThreads - 1) / kBalanceThreads;
+  const int per = (ntiles + kBalanceThreads - 1) / kBalanceThreads, len = (per + kBalanceRuns - 1) / kBalanceRuns;
   const int a = min(ntiles, tid * per), b = min(ntiles, a + per);
   if (tid < 8) {
     ctr[tid] = 0;
@@ -830,11 +831,12 @@ __device__ void balance_tiles(const MarchDev& m, const CamDev& c, const TileMap&
     sh.first[tid] = ntiles;
   }
   for (int q = tid; q < 2 * kZBuckets; q += kBalanceThreads) ctr[kZHist + q] = 0;
-  long long sum = 0;
-  for (int L = a; L < b; ++L) {
-    const int cst = tile_cost(m, c, tm, L);
-    if (L < kCostCache) sh.cost[L] = cst;
-    sum += cst;
+  long long sum = 0, cost[kBalanceRuns];
+#pragma unroll
+  for (int r = 0; r < kBalanceRuns; ++r) {
+    const int lo = min(b, a + r * len), hi = min(b, lo + len);
+    cost[r] = lo < hi ? (long long)tile_cost(m, c, tm, lo + (hi - lo) / 2) * (hi - lo) : 0;
+    sum += cost[r];
   }
   sh.scan[0][tid] = sum;
   __syncthreads();
@@ -847,11 +849,14 @@ __device__ void balance_tiles(const MarchDev& m, const CamDev& c, const TileMap&
   }
   const long long total = sh.scan[cur][kBalanceThreads - 1];
   long long run = sh.scan[cur][tid] - sum;
-  for (int L = a; L < b; ++L) {
-    const int cst = L < kCostCache ? sh.cost[L] : tile_cost(m, c, tm, L);
-    const int e = (int)min(7LL, (8 * (2 * run + cst)) / (2 * total));
-    atomicMin(&sh.first[e], L);
-    run += cst;
+#pragma unroll
+  for (int r = 0; r < kBalanceRuns; ++r) {
+    const int lo = min(b, a + r * len), hi = min(b, lo + len);
+    int e = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) e += 8 * (2 * run + cost[r]) >= 2 * total * k ? 1 : 0;
+    if (lo < hi) atomicMin(&sh.first[e], lo);
+    run += cost[r];
   }
   __syncthreads();
   if (tid == 0) {
