@@ -1018,14 +1018,18 @@ __global__ __launch_bounds__(256) void zsort_records(MarchBuf buf) {
 }
 
 // Cell order: the records scattered into z-cell order (srt).  A block takes
-// 64 pixels; wavefront w of the block takes the records k = w, w + 4, ... of
-// each (one lane per pixel; whose cells the primary march wrote to zb), so a
-// CU holds several blocks' loads in flight.  Cell b's records take entries
+// PX pixels, 256 / PX lanes each, lane s of a pixel the records k = s,
+// s + 256 / PX, ... (whose cells the primary march wrote to zb), so a CU holds
+// several blocks' loads in flight.  Cell b's records take entries
 // [B_b, B_b + n_b), B the exclusive prefix sum of the counts n; each block
 // counts its records per cell in LDS, reserves each cell's share with one
 // global atomic and writes its entries there on a second pass.  Every write
-// is bounded by its cell's range.
-constexpr int kSortPixels = 64;
+// is bounded by its cell's range.  From kSortManyPixels on the reservations of
+// all blocks queue for the cells' counters, and blocks of 128 pixels make half
+// as many (a 512^2 frame 310 -> 304 us, 304 with 256 pixels; at 256^2 64 are
+// the best: 8.7 us against 8.9 and 13.0 with 128 and 256).
+constexpr int kSortManyPixels = 131072;
+template <int PX>
 __global__ __launch_bounds__(256) void zsort_cells(MarchBuf buf) {
   __shared__ int wsum[kZBuckets / 64];
   __shared__ int bstart[kZBuckets], bend[kZBuckets], lcount[kZBuckets], lbase[kZBuckets];
@@ -1046,10 +1050,9 @@ __global__ __launch_bounds__(256) void zsort_cells(MarchBuf buf) {
   for (int w = 0; w < (tid >> 6); ++w) inc += wsum[w];
   bstart[tid] = inc - n;
   bend[tid] = inc;
-  // S lanes per pixel: lane tid takes records tid / kSortPixels + S j of
-  // pixel tid % kSortPixels
-  constexpr int S = 256 / kSortPixels;
-  const int p = blockIdx.x * kSortPixels + tid % kSortPixels, k1 = tid / kSortPixels;
+  // S lanes per pixel: lane tid takes records tid / PX + S j of pixel tid % PX
+  constexpr int S = 256 / PX;
+  const int p = blockIdx.x * PX + tid % PX, k1 = tid / PX;
   const int cnt = p < buf.P ? min(buf.cnt[p], buf.K) : 0;
   // U of the lane's records at a time, their loads and LDS atomics issued
   // together (one record after the other leaves the lane waiting on each load)
@@ -1800,7 +1803,10 @@ hipError_t launch_march(const MarchDev& m0, const CamDev& cam, const MarchBuf& b
   if (m.zorder == kOrderCells) {
     // the scatter with one lane per pixel; the light marches with one
     // workgroup per CU (the planes take most of its LDS)
-    hipLaunchKernelGGL(zsort_cells, dim3((buf.P + kSortPixels - 1) / kSortPixels), dim3(256), 0, s, buf);
+    if (buf.P >= kSortManyPixels)
+      hipLaunchKernelGGL(zsort_cells<128>, dim3((buf.P + 128 - 1) / 128), dim3(256), 0, s, buf);
+    else
+      hipLaunchKernelGGL(zsort_cells<64>, dim3((buf.P + 63) / 64), dim3(256), 0, s, buf);
     hipLaunchKernelGGL(march_lights_cells, dim3(8 * cell_blocks_per_xcd()), dim3(kCellThreads),
                        cell_planes_bytes(m.nx, m.ny), s, m, cam, buf);
   } else if (m.zorder) {
