@@ -12,7 +12,7 @@
 // than the fp32 instruction's (lightmaps of 8 x 256^2, 4 levels, base 32:
 // 2.5e-7 against 6.8e-7).  Six bf16 products take 96 cycles per 16 x 16 x 32
 // block against 256 for fp32's.  Measured on that network: inference 1805 ->
-// 971 us (175 TFLOP/s of fp32 products), one 256^2 frame 355 -> 296 us; the
+// 971 us (175 TFLOP/s of fp32 products), one 256^2 frame 355 -> 290 us; the
 // data gradients of a training batch, with the masking, pooling and
 // concatenation passes that they now carry, 2140 -> 1065 us.
 //
