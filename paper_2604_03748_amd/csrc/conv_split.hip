@@ -24,10 +24,10 @@
 // row's) three 16-channel pieces in 96 bytes without padding: the 16 lanes
 // that one LDS cycle serves (rows 0-3 and 12-15 of one lane group, 4-11 of
 // the next) then lie on distinct banks.  (Rows padded to 112 bytes looked
-// safer and took two cycles: 1023 -> 971 us for the inference above.)  The product is taken
-// transposed (channels as MFMA rows), so a lane ends with four consecutive
-// channels of one pixel: 16-byte stores, and the gradient's routing (see
-// Route) on whole vectors.
+// safer and took two cycles: 1023 -> 971 us for the inference above.)  The
+// product is taken transposed (channels as MFMA rows), so a lane ends with
+// four consecutive channels of one pixel: 16-byte stores, and the gradient's
+// routing (see Route) on whole vectors.
 #include <type_traits>
 
 #include "first_layer.h"
@@ -230,7 +230,8 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
   // operands are read among the step before's products and the loads issued
   // among the first steps' in 4-row tiles, whose few wavefronts hide neither
   // (2040 -> 1290 cycles for 60 products by the reads alone; the
-  // base-16 network's small images 65 -> 62 us, a 256^2 frame 300 -> 294).  Taller tiles gain nothing.
+  // base-16 network's small images 65 -> 62 us, a 256^2 frame 300 -> 294).
+  // Taller tiles gain nothing.
   auto products = [&](int ch, auto more) __attribute__((always_inline)) {
     if constexpr (decltype(more)::value) fetch(ch + 1);
 #pragma unroll
@@ -442,7 +443,8 @@ hipError_t launch_mf(const ConvArgs& a, hipStream_t s, const HeadFuse* head) {
 // product (a 4-row tile's reads take longer than its products) and split
 // the weights for more pixels: 8 x 256^2 on the 4-level base-32 network took
 // 1336 us with the 4-row tiles that one image takes in the deep levels, 1053
-// with these.
+// with these.  For one image 512 is the best as well: a 256^2 frame takes 294
+// us, 300 with 8-row tiles from 256 workgroups on and 304 from 1024 on.
 int tile_rows(const ConvArgs& a, int tallest) {
   auto wgs = [&](int th) {
     return (long)((a.W + kTW - 1) / kTW) * ((a.H + th - 1) / th) * a.B * a.n_tiles * a.splits;
