@@ -290,10 +290,11 @@ LNM_API size_t lnm_frame_workspace_bytes(lnm_net net, const lnm_volume* vol, con
  * same frame, bit for bit, computed in the library's static workspace
  * instead of a caller-provided one.  It allocates no device memory and
  * calls no allocating routine.  The caller still provides guide, lightmaps
- * and rgba (rgba may be NULL) as for lnm_frame.  A frame whose
- * lnm_frame_workspace_bytes exceeds LNM_STATIC_SCRATCH_BYTES (the 128^3 grid
- * at 256 x 256 takes about 123 MiB) returns LNM_ERR_SHAPE with nothing
- * enqueued.  All calls on one device share its one workspace: calls that
+ * and rgba (rgba may be NULL) as for lnm_frame.  A frame that does not fit in
+ * LNM_STATIC_SCRATCH_BYTES (the 128^3 grid at 256 x 256 takes about 123 MiB),
+ * without the optional copy of the grid that lnm_frame_workspace_bytes may
+ * count in z order (see lnm_march_workspace_bytes), returns LNM_ERR_SHAPE
+ * with nothing enqueued.  All calls on one device share its one workspace: calls that
  * may overlap on a device (other streams, other threads, other contexts)
  * race and must be serialised by the caller.  Nothing needs clearing between
  * calls: every byte the frame reads is written earlier in the same call. */

@@ -567,7 +567,7 @@ lnm_status frame_impl(lnm_ctx_s* ctx, const lnm_net_s* net, const lnm_volume* vo
 }
 
 size_t frame_workspace_bytes(const lnm_net_s* net, const lnm_volume* vol, const lnm_camera* cam,
-                             const lnm_march_params* prm) {
+                             const lnm_march_params* prm, size_t ws_bytes) {
   MarchDev m;
   CamDev c;
   if (!net || march_setup(vol, cam, prm, &m, &c)) return 0;
@@ -575,7 +575,7 @@ size_t frame_workspace_bytes(const lnm_net_s* net, const lnm_volume* vol, const 
   if (c.H % div || c.W % div) return 0;
   // the march's records are dead once the guide is written, so the U-Net
   // activations reuse the same bytes
-  return std::max(march_scratch_bytes(m, march_capacity(m), c.W, c.H), plan_workspace(net, 1, c.H, c.W).bytes);
+  return std::max(fit_march(&m, march_capacity(m), c.W, c.H, ws_bytes), plan_workspace(net, 1, c.H, c.W).bytes);
 }
 
 }  // namespace lnm

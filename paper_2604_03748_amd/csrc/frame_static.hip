@@ -32,7 +32,7 @@ extern "C" lnm_status lnm_frame_static(lnm_ctx ctx, lnm_net net, const lnm_volum
                                        float* guide, float* lightmaps, float* rgba, void* stream) {
   if (!ctx) return fail(LNM_ERR_ARG, "ctx is NULL");
   if (!ctx->static_scratch) return fail(LNM_ERR_DEVICE, "the context has no static workspace");
-  const size_t need = frame_workspace_bytes(net, vol, cam, prm);
+  const size_t need = frame_workspace_bytes(net, vol, cam, prm, LNM_STATIC_SCRATCH_BYTES);
   if (need > (size_t)LNM_STATIC_SCRATCH_BYTES)
     return fail(LNM_ERR_SHAPE, "frame needs " + std::to_string(need) + " bytes of workspace, more than the " +
                                    std::to_string((size_t)LNM_STATIC_SCRATCH_BYTES) +

@@ -392,8 +392,10 @@ lnm_status check_infer(const lnm_net_s* net, int B, int H, int W, size_t ws_byte
 lnm_status frame_impl(lnm_ctx_s* ctx, const lnm_net_s* net, const lnm_volume* vol, const lnm_camera* cam,
                       const lnm_march_params* prm, const lnm_light* lights, int n_lights, float* guide,
                       float* lightmaps, float* rgba, void* workspace, size_t ws_bytes, void* stream);
+// (the size the frame takes in a workspace of ws_bytes: the march drops the
+// plane pairs where only that fits)
 size_t frame_workspace_bytes(const lnm_net_s* net, const lnm_volume* vol, const lnm_camera* cam,
-                             const lnm_march_params* prm);
+                             const lnm_march_params* prm, size_t ws_bytes = SIZE_MAX);
 // Device address of the library's static frame workspace on the current
 // device (frame_static.hip); call with that device current.
 hipError_t static_scratch_address(void** out);
