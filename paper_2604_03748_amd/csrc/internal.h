@@ -53,6 +53,7 @@ struct MarchDev {
   // entry ((k (ny + 2) + j) (nx + 2) + i) is the two values of grid planes
   // k - 1 and k at column (i - 1, j - 1), zero outside the grid
   int pairs;
+  int pair_shift;     // on pairs the records are sorted by z cell >> pair_shift
   const float* pair;  // in the scratch
 };
 
@@ -87,7 +88,7 @@ struct TileMap {
 // order), start[0..8] of the band tile ranges from kBandStart, the record
 // count of each z bucket from kZHist and the z-order scatter cursors from
 // kZCursor.
-constexpr int kBrickSlot = 128;
+constexpr int kBrickSlot = 128, kBrickShift = 2;  // a brick is 1 << kBrickShift cells wide
 constexpr int kTile = 8;
 constexpr int kUnitNext = 8, kBandStart = 16;
 constexpr int kZBuckets = 256;

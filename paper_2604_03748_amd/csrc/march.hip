@@ -541,16 +541,20 @@ __device__ __forceinline__ float light_transmittance_lds(const MarchDev& m, V3 x
 // z bucket of a sample point: its trilinear cell k' = floor(gz) + 1 (the
 // cell between grid planes k' - 1 and k'), in z order on bricks grouped by
 // brick layer (the bricks hold cells in layers k' / 4), capped at the last
-// bucket.  (On plane pairs one bucket per cell: 1275 us of light marches and 91
+// bucket.  On plane pairs one bucket per cell (1275 us of light marches and 91
 // of sorting at 256^3 / 1024^2 against 1338 and 83 with layers; a pixel's
-// records kept together instead of its neighbours': 1304 and 131.)  A
+// records kept together instead of its neighbours': 1304 and 131) or, on grids
+// of more cells than buckets, per 2 or 4 of them (pair_shift): with the rest
+// of the cells in the last bucket, unsorted, 384^3 / 512^2 took 5.2 ms instead
+// of 2.4.  A
 // side light has no z component, so a light march stays in its sample's
 // cell (the fallback lights of a ray along z and the left/right set do not;
 // the order then only loses locality).
 __device__ __forceinline__ int z_bucket(const MarchDev& m, float pz) {
   const float gz = fminf(fmaxf(fmaf(pz, (float)m.nz, -0.5f), -1.0f), (float)m.nz);
   const int cell = (int)floorf(gz) + 1;
-  return min(m.zorder == kOrderCells || m.pairs ? cell : cell >> 2, kZBuckets - 1);
+  const int shift = m.zorder == kOrderCells ? 0 : m.pairs ? m.pair_shift : kBrickShift;
+  return min(cell >> shift, kZBuckets - 1);
 }
 
 __device__ __forceinline__ void tile_origin(const TileMap& tm, int L, int* tx, int* ty) {
@@ -1785,6 +1789,8 @@ hipError_t launch_march(const MarchDev& m0, const CamDev& cam, const MarchBuf& b
   const TileMap tm = tile_map(cam);
   if (m.pairs) {  // build the plane pairs in the scratch; one extra block balances the bands
     m.pair = buf.pair;
+    m.pair_shift = 0;
+    while (m.pair_shift < kBrickShift && (m.nz - 1) >> m.pair_shift >= kZBuckets) ++m.pair_shift;
     const int plane = (m.nx + 2) * (m.ny + 2);
     hipLaunchKernelGGL(pairs_balance, dim3((plane + 255) / 256, m.nz / kPairZ + 2), dim3(256), 0, s, m, cam, tm, buf.ctr,
                        buf.pair);
