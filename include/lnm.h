@@ -70,8 +70,8 @@ typedef struct lnm_net_s* lnm_net; /* host descriptor of a packed network */
  * The march reads the grid as 4^3-cell bricks: by default each march call
  * builds them in its workspace; a caller that marches the same grid many
  * times may build them once with lnm_make_bricks and pass them in `bricks`
- * (the march then trusts that they were made from `density` and these
- * dimensions, and needs a smaller workspace). */
+ * (the march then trusts that they were made from `density`, which it may
+ * still read, and these dimensions, and needs a smaller workspace). */
 typedef struct {
   const float* density; /* device, [nz][ny][nx], x fastest */
   int32_t nx, ny, nz;   /* each >= 1 */
@@ -177,8 +177,9 @@ LNM_API lnm_status lnm_make_bricks(lnm_ctx ctx, const lnm_volume* vol, float* br
  * box diagonal over h) and their light terms, in z order (prm->work_order)
  * also a z-bucket byte and a sorted-list entry per record, plus the bricked
  * grid unless vol->bricks is given, or in z order a copy of about that size
- * that its light marches read faster (a workspace without room for it is
- * accepted and gives the same map from the bricks); 0 on invalid arguments. */
+ * that its light marches read faster (with vol->bricks only where the view
+ * may repay the copy; a workspace without room for it is accepted and gives
+ * the same map from the bricks); 0 on invalid arguments. */
 LNM_API size_t lnm_march_workspace_bytes(const lnm_volume* vol, const lnm_camera* cam,
                                          const lnm_march_params* prm);
 

@@ -130,7 +130,7 @@ static lnm_status march_setup(const lnm_volume* vol, const lnm_camera* cam, cons
   m->brick = vol->bricks;  // NULL: launch_march builds them in its scratch
   m->nbx = m->nby = m->nbz = 0;
   m->pair = nullptr;
-  m->pairs = march_pairs(*m, c->W, c->H);
+  m->pairs = march_pairs(m, *c);
   return LNM_OK;
 }
 

@@ -52,8 +52,9 @@ struct MarchDev {
   // z order: the march reads plane pairs instead of bricks (march_pairs):
   // entry ((k (ny + 2) + j) (nx + 2) + i) is the two values of grid planes
   // k - 1 and k at column (i - 1, j - 1), zero outside the grid
-  int pairs;
-  int pair_shift;     // on pairs the records are sorted by z cell >> pair_shift
+  int pairs;          // kPairsNone, kPairsAlways, kPairsAsked (march_pairs)
+  int pair_hits;      // kPairsAsked: see pairs_repay
+  int pair_shift;     // records are sorted by z cell >> pair_shift on pairs
   const float* pair;  // in the scratch
 };
 
@@ -85,12 +86,13 @@ struct TileMap {
 // of a 4^3-cell brick and the next layer, padded).  kTile: side of the
 // primary march's screen tiles.  The counter block (ints): the 8 band
 // counters, the light marches' per-XCD next-unit counters from kUnitNext (z
-// order), start[0..8] of the band tile ranges from kBandStart, the record
+// order), start[0..8] of the band tile ranges from kBandStart, whether the march
+// reads plane pairs at kPairsUsed (where it was asked), the record
 // count of each z bucket from kZHist and the z-order scatter cursors from
 // kZCursor.
 constexpr int kBrickSlot = 128, kBrickShift = 2;  // a brick is 1 << kBrickShift cells wide
 constexpr int kTile = 8;
-constexpr int kUnitNext = 8, kBandStart = 16;
+constexpr int kUnitNext = 8, kBandStart = 16, kPairsUsed = 25;
 constexpr int kZBuckets = 256;
 constexpr int kZHist = 32, kZCursor = kZHist + kZBuckets;
 constexpr size_t kCounterBytes = 4 * (kZCursor + kZBuckets);
@@ -110,8 +112,9 @@ constexpr int kOrderBands = 0, kOrderLayers = 1, kOrderCells = 2;
 int march_order(int work_order, int light_set, int nx, int ny, int nz);
 // AUTO's z cells become bands when the light marches are short (world step h).
 int march_order_short(int work_order, int order, float h);
-// Whether a march of a W x H view should read plane pairs, and their bytes.
-bool march_pairs(const MarchDev& m, int W, int H);
+// Whether a march should read plane pairs (and m.pair_hits), and their bytes.
+constexpr int kPairsNone = 0, kPairsAlways = 1, kPairsAsked = 2;
+int march_pairs(MarchDev* m, const CamDev& c);
 size_t pairs_bytes(int nx, int ny, int nz);
 // Scratch of one march; the plane pairs are part of it when m.pairs is set,
 // else the bricked grid unless m.brick is.

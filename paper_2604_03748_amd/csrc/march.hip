@@ -160,6 +160,11 @@ __device__ __forceinline__ PairVals pair_load(const MarchDev& m, uint32_t at) {
   __builtin_memcpy(c.r1, p + sizeof(float2) * (m.nx + 2) + 8u * at, 16);
   return c;
 }
+// Whether the march reads the pairs (PAIRS: its MarchDev::pairs).
+template <int PAIRS>
+__device__ __forceinline__ bool reads_pairs(const MarchBuf& buf) {
+  return PAIRS == kPairsAlways || (PAIRS == kPairsAsked && buf.ctr[kPairsUsed] != 0);
+}
 __device__ __forceinline__ float sample_sigma_pairs(const MarchDev& m, float px, float py, float pz) {
   const float gx = fmaf(px, (float)m.nx, -0.5f), gy = fmaf(py, (float)m.ny, -0.5f), gz = fmaf(pz, (float)m.nz, -0.5f);
   const bool inside = gx > -1.0f && gy > -1.0f && gz > -1.0f && gx < (float)m.nx && gy < (float)m.ny &&
@@ -550,11 +555,10 @@ __device__ __forceinline__ float light_transmittance_lds(const MarchDev& m, V3 x
 // side light has no z component, so a light march stays in its sample's
 // cell (the fallback lights of a ray along z and the left/right set do not;
 // the order then only loses locality).
-__device__ __forceinline__ int z_bucket(const MarchDev& m, float pz) {
+__device__ __forceinline__ int z_bucket(const MarchDev& m, int zshift, float pz) {
   const float gz = fminf(fmaxf(fmaf(pz, (float)m.nz, -0.5f), -1.0f), (float)m.nz);
   const int cell = (int)floorf(gz) + 1;
-  const int shift = m.zorder == kOrderCells ? 0 : m.pairs ? m.pair_shift : kBrickShift;
-  return min(cell >> shift, kZBuckets - 1);
+  return min(cell >> zshift, kZBuckets - 1);
 }
 
 __device__ __forceinline__ void tile_origin(const TileMap& tm, int L, int* tx, int* ty) {
@@ -646,7 +650,7 @@ __device__ __forceinline__ float quad_last(float v) { return __int_as_float(quad
 template <bool PAIRS>
 __device__ __forceinline__ void primary_tile(const MarchDev& m, const CamDev& c, const TileMap& tm,
                                              const MarchBuf& buf, float* __restrict__ guide, int tile, int band,
-                                             int2* __restrict__ list, int* zh, int* agg) {
+                                             int2* __restrict__ list, int* zh, int* agg, int zshift) {
   int i, j;
   quad_pixel(tm, tile, &i, &j);
   const int s = threadIdx.x & 3;
@@ -714,7 +718,7 @@ __device__ __forceinline__ void primary_tile(const MarchDev& m, const CamDev& c,
       buf.a[r] = Tprev * alpha;
       buf.tp[r] = Tprev;
       if (m.zorder) {
-        const int zk = z_bucket(m, pz);
+        const int zk = z_bucket(m, zshift, pz);
         buf.zb[r] = (uint8_t)zk;
         atomicAdd(&zh[zk], 1);
       }
@@ -774,11 +778,13 @@ __device__ __forceinline__ void primary_tile(const MarchDev& m, const CamDev& c,
 // owns.  The band's blocks take its tiles in turn.
 // In z order the block also counts its records per z bucket in LDS and adds
 // them to the global counts at the end.
-template <bool PAIRS>
+template <int PAIRS>
 __global__ __launch_bounds__(256, 4) void march_primary(MarchDev m, CamDev c, TileMap tm, MarchBuf buf,
                                                      float* __restrict__ guide) {
   __shared__ int zh[kZBuckets];
   __shared__ int agg[5];
+  const bool pairs = reads_pairs<PAIRS>(buf);
+  const int zshift = m.zorder == kOrderCells ? 0 : pairs ? m.pair_shift : kBrickShift;
   if (m.zorder) {
     for (int q = threadIdx.x; q < kZBuckets; q += 256) zh[q] = 0;
     __syncthreads();
@@ -787,8 +793,12 @@ __global__ __launch_bounds__(256, 4) void march_primary(MarchDev m, CamDev c, Ti
   const int* start = buf.ctr + kBandStart;
   const int lo = start[band], hi = start[band + 1];
   int2* list = buf.rec ? buf.rec + (size_t)lo * (kTile * kTile) * (size_t)buf.K : nullptr;
-  for (int L = lo + (int)(blockIdx.x >> 3); L < hi; L += slots)
-    primary_tile<PAIRS>(m, c, tm, buf, guide, L, band, list, zh, agg);
+  for (int L = lo + (int)(blockIdx.x >> 3); L < hi; L += slots) {
+    if (pairs)
+      primary_tile<true>(m, c, tm, buf, guide, L, band, list, zh, agg, zshift);
+    else
+      primary_tile<false>(m, c, tm, buf, guide, L, band, list, zh, agg, zshift);
+  }
   if (m.zorder) {
     __syncthreads();
     for (int q = threadIdx.x; q < kZBuckets; q += 256)
@@ -899,34 +909,55 @@ __global__ __launch_bounds__(256) void relayout_balance(MarchDev m, CamDev c, Ti
 // (ny + 2) x (nx + 2) border plane over kPairZ cells, each grid value read once
 // and carried to the next cell, so loads and stores run along x.  As in
 // relayout_balance, one extra z slice in front holds the balance block.
-// Bound by memory (256^3: 67 MB read and 137 MB written in 107 us, as the
-// bricks took).
+// Bound by memory (256^3: 67 MB read and 137 MB written in 35 us, 5.8 TB/s).
 constexpr int kPairZ = 8;
+//
+// Beside bricks of the caller (kPairsAsked) every workgroup first looks at the
+// same 256 points of the grid: where fewer than pair_hits of them hold any
+// density, the march records too few samples to repay the copy (march_pairs)
+// and stays on the bricks.  This takes 1 to 2 us of the copy's 35 at 256^3.
+__device__ __forceinline__ bool pairs_repay(const MarchDev& m) {
+  // a low-discrepancy lattice (steps 1/g, 1/g^2, 1/g^3, g^4 = g + 1)
+  const float s = (float)threadIdx.x;
+  const int i = (int)(__builtin_amdgcn_fractf(0.5f + s * 0.8191725f) * (float)m.nx);
+  const int j = (int)(__builtin_amdgcn_fractf(0.5f + s * 0.6710436f) * (float)m.ny);
+  const int k = (int)(__builtin_amdgcn_fractf(0.5f + s * 0.5497005f) * (float)m.nz);
+  const float v = m.rho[((size_t)min(k, m.nz - 1) * m.ny + min(j, m.ny - 1)) * m.nx + min(i, m.nx - 1)];
+  return __syncthreads_count(m.sigma_scale * v != 0.0f) >= m.pair_hits;
+}
+template <bool ASK>
 __global__ __launch_bounds__(256) void pairs_balance(MarchDev m, CamDev c, TileMap tm, int* __restrict__ ctr,
                                                      float* __restrict__ pair) {
   __shared__ BalanceLds sh;
+  const bool repay = !ASK || pairs_repay(m);
   if (blockIdx.y == 0) {
-    if (blockIdx.x == 0) balance_tiles(m, c, tm, ctr, sh);
+    if (blockIdx.x == 0) {
+      if (ASK && threadIdx.x == 0) ctr[kPairsUsed] = repay;
+      balance_tiles(m, c, tm, ctr, sh);
+    }
     return;
   }
+  if (!repay) return;
   const int row = m.nx + 2, plane = (m.ny + 2) * row;
-  const int e = blockIdx.x * 256 + threadIdx.x, k0 = ((int)blockIdx.y - 1) * kPairZ;
+  const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= plane) return;
   const int j = e / row - 1, i = e - (j + 1) * row - 1;
   const bool in = i >= 0 && i < m.nx && j >= 0 && j < m.ny;
   const size_t ps = (size_t)m.nx * m.ny;
   const float* src = m.rho + (in ? (size_t)j * m.nx + i : 0);
-  float v[kPairZ + 1];  // grid planes k0 - 1 .. k0 + kPairZ - 1
+  for (int k0 = ((int)blockIdx.y - 1) * kPairZ; k0 <= m.nz; k0 += ((int)gridDim.y - 1) * kPairZ) {
+    float v[kPairZ + 1];  // grid planes k0 - 1 .. k0 + kPairZ - 1
 #pragma unroll
-  for (int q = 0; q <= kPairZ; ++q) {
-    const int k = k0 + q - 1;
-    v[q] = src[(size_t)min(max(k, 0), m.nz - 1) * ps];
-    if (!in || k < 0 || k >= m.nz) v[q] = 0.0f;
+    for (int q = 0; q <= kPairZ; ++q) {
+      const int k = k0 + q - 1;
+      v[q] = src[(size_t)min(max(k, 0), m.nz - 1) * ps];
+      if (!in || k < 0 || k >= m.nz) v[q] = 0.0f;
+    }
+#pragma unroll
+    for (int q = 0; q < kPairZ; ++q)
+      if (k0 + q <= m.nz)
+        reinterpret_cast<float2*>(pair)[(size_t)(k0 + q) * plane + e] = make_float2(v[q], v[q + 1]);
   }
-#pragma unroll
-  for (int q = 0; q < kPairZ; ++q)
-    if (k0 + q <= m.nz)
-      reinterpret_cast<float2*>(pair)[(size_t)(k0 + q) * plane + e] = make_float2(v[q], v[q + 1]);
 }
 
 // Entry r of the band lists concatenated in band order.
@@ -1105,7 +1136,7 @@ __global__ __launch_bounds__(256) void zsort_cells(MarchBuf buf) {
 // the bricks in use at a time are about one layer).  Result: T toward the
 // top (or first side) light in tl[0][k][pixel], toward the bottom (second
 // side) light in tl[1][k][pixel].
-template <bool Z, bool PAIRS>
+template <bool Z, int PAIRS>
 __global__ __launch_bounds__(256) void march_lights(MarchDev m, CamDev c, MarchBuf buf, int slots) {
   int count[8], total = 0;
 #pragma unroll
@@ -1117,6 +1148,7 @@ __global__ __launch_bounds__(256) void march_lights(MarchDev m, CamDev c, MarchB
   const int lo = (int)((long)total * part / 8), hi = (int)((long)total * (part + 1) / 8);
   const int units = 2 * ((hi - lo + 255) / 256);
   const int R = gridDim.x >> 3;
+  const bool pairs = reads_pairs<PAIRS>(buf);
   __shared__ int s_unit;
   for (int unit = blockIdx.x >> 3; unit < units;) {
     do {  // one unit; `continue` leaves it
@@ -1137,7 +1169,7 @@ __global__ __launch_bounds__(256) void march_lights(MarchDev m, CamDev c, MarchB
       if (light) l = v3(-l.x, -l.y, -l.z);
       const V3 x = v3(o.x + t * d.x, o.y + t * d.y, o.z + t * d.z);
       float T;
-      if constexpr (PAIRS)
+      if (pairs)
         T = l.z == 0.0f ? light_transmittance_pairs<true>(m, x, l) : light_transmittance_pairs<false>(m, x, l);
       else
         T = l.z == 0.0f ? light_transmittance_batched<true>(m, x, l) : light_transmittance_batched<false>(m, x, l);
@@ -1721,6 +1753,7 @@ __global__ __launch_bounds__(64) void reference_kernel(MarchDev m, CamDev c, int
 
 }  // namespace
 
+constexpr int kPairBlocks = 2048;       // workgroups of pairs_balance that fit at once
 constexpr size_t kLightSlots = 512;  // workgroups per band in march_lights (band order)
 
 hipError_t launch_relayout(const MarchDev& m, float* bricks, hipStream_t s) {
@@ -1753,7 +1786,7 @@ static TileMap tile_map(const CamDev& c) {
 
 // Light-march blocks per XCD in z order: as many as are resident at once
 // (the occupancy of march_lights on one XCD's CUs), at least one.
-template <bool PAIRS>
+template <int PAIRS>
 static int light_blocks_per_xcd() {
   static int n = 0;
   if (n == 0) {
@@ -1789,11 +1822,12 @@ hipError_t launch_march(const MarchDev& m0, const CamDev& cam, const MarchBuf& b
   const TileMap tm = tile_map(cam);
   if (m.pairs) {  // build the plane pairs in the scratch; one extra block balances the bands
     m.pair = buf.pair;
-    m.pair_shift = 0;
-    while (m.pair_shift < kBrickShift && (m.nz - 1) >> m.pair_shift >= kZBuckets) ++m.pair_shift;
-    const int plane = (m.nx + 2) * (m.ny + 2);
-    hipLaunchKernelGGL(pairs_balance, dim3((plane + 255) / 256, m.nz / kPairZ + 2), dim3(256), 0, s, m, cam, tm, buf.ctr,
-                       buf.pair);
+    const int cols = ((m.nx + 2) * (m.ny + 2) + 255) / 256, slabs = m.nz / kPairZ + 1;
+    if (m.pairs == kPairsAsked)  // no more workgroups than fit at once, as each looks at the grid first
+      hipLaunchKernelGGL(pairs_balance<true>, dim3(cols, 1 + std::min(slabs, std::max(1, kPairBlocks / cols))),
+                         dim3(256), 0, s, m, cam, tm, buf.ctr, buf.pair);
+    else
+      hipLaunchKernelGGL(pairs_balance<false>, dim3(cols, 1 + slabs), dim3(256), 0, s, m, cam, tm, buf.ctr, buf.pair);
   } else if (!m.brick) {  // the bricks, likewise
     m.brick = buf.brick;
     hipLaunchKernelGGL(relayout_balance,
@@ -1802,10 +1836,10 @@ hipError_t launch_march(const MarchDev& m0, const CamDev& cam, const MarchBuf& b
   } else {
     hipLaunchKernelGGL(march_balance, dim3(1), dim3(kBalanceThreads), 0, s, m, cam, tm, buf.ctr);
   }
-  if (m.pairs)
-    hipLaunchKernelGGL(march_primary<true>, dim3(8 * tm.per_xcd), dim3(256), 0, s, m, cam, tm, buf, guide);
-  else
-    hipLaunchKernelGGL(march_primary<false>, dim3(8 * tm.per_xcd), dim3(256), 0, s, m, cam, tm, buf, guide);
+  const auto primary = m.pairs == kPairsAsked    ? march_primary<kPairsAsked>
+                       : m.pairs == kPairsAlways ? march_primary<kPairsAlways>
+                                                 : march_primary<kPairsNone>;
+  hipLaunchKernelGGL(primary, dim3(8 * tm.per_xcd), dim3(256), 0, s, m, cam, tm, buf, guide);
   if (m.zorder == kOrderCells) {
     // the scatter with one lane per pixel; the light marches with one
     // workgroup per CU (the planes take most of its LDS)
@@ -1817,18 +1851,20 @@ hipError_t launch_march(const MarchDev& m0, const CamDev& cam, const MarchBuf& b
                        cell_planes_bytes(m.nx, m.ny), s, m, cam, buf);
   } else if (m.zorder) {
     // the blocks resident at once; each loops over units of its XCD's range
-    const size_t resident = m.pairs ? light_blocks_per_xcd<true>() : light_blocks_per_xcd<false>();
+    const size_t resident = m.pairs == kPairsAsked    ? light_blocks_per_xcd<kPairsAsked>()
+                            : m.pairs == kPairsAlways ? light_blocks_per_xcd<kPairsAlways>()
+                                                      : light_blocks_per_xcd<kPairsNone>();
     const int slots = (int)std::min<size_t>((buf.cap + 255) / 256, resident);
     hipLaunchKernelGGL(zsort_records, dim3(8 * slots), dim3(256), 0, s, buf);
-    if (m.pairs)
-      hipLaunchKernelGGL((march_lights<true, true>), dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
-    else
-      hipLaunchKernelGGL((march_lights<true, false>), dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
+    const auto lights = m.pairs == kPairsAsked    ? march_lights<true, kPairsAsked>
+                        : m.pairs == kPairsAlways ? march_lights<true, kPairsAlways>
+                                                  : march_lights<true, kPairsNone>;
+    hipLaunchKernelGGL(lights, dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
   } else {
     // enough workgroups to fill the chip a few times over; each loops over
     // its eighth of the records
     const int slots = (int)std::min<size_t>((buf.cap + 255) / 256, kLightSlots);
-    hipLaunchKernelGGL((march_lights<false, false>), dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
+    hipLaunchKernelGGL((march_lights<false, kPairsNone>), dim3(8 * slots), dim3(256), 0, s, m, cam, buf, slots);
   }
   hipLaunchKernelGGL(march_accumulate, dim3((buf.P + 255) / 256), dim3(256), 0, s, m, buf, guide);
   return hipGetLastError();

@@ -61,16 +61,62 @@ int march_order(int work_order, int light_set, int nx, int ny, int nz) {
 // its cell's pair of planes) instead of a brick's four 8-byte ones, and the
 // gathers cost by the instruction (17 to 38 cycles for 64 lanes, 8 bytes and
 // 16 alike), which bounds the z order's light marches: 1950 -> 1275 us at 256^3
-// / 1024^2, two such marches of a serving batch 919 -> 695 us.  Building them
-// takes what building the bricks takes; where the caller gives bricks, the
-// marches of views from 0.002 pixels per voxel on win it back (256^3: 310
-// against 337 us at 192^2, 266 against 207 at 128^2; 160^3: 84 against 88 at
-// 96^2, 75 against 68 at 64^2).  In cell order, whose light marches read LDS,
-// they gained nothing over the bricks.
+// / 1024^2.  Building them takes what building the bricks takes.  In cell
+// order, whose light marches read LDS, they gained nothing over the bricks.
+//
+// Where the caller gives bricks, the light marches' samples have to repay the
+// copy.  Their number goes with the primary samples inside the grid (pixels x
+// mean chord / h), the share of them that meet density (pair_hits of 256
+// points, looked at on the device) and the steps of a light march beyond the
+// dozen that cost alike either way: the copy is made from kPairCost voxels'
+// worth on.  140 marches over 136^3 to 256^3 grids, cubic and not, 64 to 512
+// pixels a side, both projections, steps of 2, 4 and 8 voxels, full and nearly
+// empty grids, buffers cold: below 1.2 products per voxel pairs took 0.83 to
+// 1.38 of the bricks' time, above it 0.63 to 0.99 (256^3 at 512^2 0.86).  (The
+// bricks for the primary march and the copy once its records are counted: 0.82
+// to 1.04 there, as both copies of the grid are then read.)
 size_t pairs_bytes(int nx, int ny, int nz) { return 2 * sizeof(float) * (size_t)(nx + 2) * (ny + 2) * (nz + 1); }
-bool march_pairs(const MarchDev& m, int W, int H) {
-  if (m.zorder != kOrderLayers || pairs_bytes(m.nx, m.ny, m.nz) > 0xFFFFFFFFull) return false;
-  return !m.brick || (double)W * H >= 0.002 * m.nx * m.ny * m.nz;
+// Mean length of a view's rays inside the support box, from 8 x 8 of them.
+static double mean_chord(const MarchDev& m, const CamDev& c) {
+  const double n[3] = {(double)m.nx, (double)m.ny, (double)m.nz};
+  double sum = 0.0;
+  for (int p = 0; p < 64; ++p) {
+    const double sx = ((p % 8 + 0.5) / 4 - 1) * c.aspect, sy = 1 - (p / 8 + 0.5) / 4;
+    double o[3], d[3], len = 0.0;
+    for (int a = 0; a < 3; ++a) {
+      const double side = sx * c.r[a] + sy * c.u[a];
+      o[a] = c.eye[a] + (c.proj == LNM_ORTHOGRAPHIC ? c.half_extent * side : 0.0);
+      d[a] = c.f[a] + (c.proj == LNM_ORTHOGRAPHIC ? 0.0 : c.tan_half * side);
+      len += d[a] * d[a];
+    }
+    double t0 = 0.0, t1 = INFINITY;
+    for (int a = 0; a < 3; ++a) {
+      const double lo = -0.5 / n[a] - o[a], hi = 1 + 0.5 / n[a] - o[a];
+      if (d[a] == 0.0) {
+        if (lo > 0 || hi < 0) t1 = -1.0;
+        continue;
+      }
+      t0 = std::max(t0, std::min(lo / d[a], hi / d[a]));
+      t1 = std::min(t1, std::max(lo / d[a], hi / d[a]));
+    }
+    if (t1 > t0) sum += (t1 - t0) * std::sqrt(len);
+  }
+  return sum / 64;
+}
+
+constexpr double kPairCost = 1.2;
+
+int march_pairs(MarchDev* m, const CamDev& c) {
+  m->pair_hits = m->pair_shift = 0;
+  if (m->zorder != kOrderLayers || pairs_bytes(m->nx, m->ny, m->nz) > 0xFFFFFFFFull) return kPairsNone;
+  while (m->pair_shift < kBrickShift && (m->nz - 1) >> m->pair_shift >= kZBuckets) ++m->pair_shift;
+  if (!m->brick) return kPairsAlways;
+  const double steps = 1.0 / m->h, voxels = (double)m->nx * m->ny * m->nz;
+  const double samples = (double)c.W * c.H * mean_chord(*m, c) * steps * std::max(steps - 12.0, steps / 8.0);
+  const double hits = std::ceil(256.0 * kPairCost * voxels / samples);
+  if (!(hits <= 256.0)) return kPairsNone;
+  m->pair_hits = (int)hits;
+  return kPairsAsked;
 }
 
 // Light marches of at most 20 steps across the grid are too short to pay for

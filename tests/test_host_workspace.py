@@ -86,3 +86,21 @@ def test_static_frame_beyond_the_workspace(host, net):
     v, c = volume(256, True), camera(512, 512)
     st = host.lnm_frame_static(ctx, handle, C.byref(v), C.byref(c), C.byref(prm), None, 0, ANY, ANY, None, None)
     assert st == lnm.LNM_ERR_SHAPE and b"static workspace" in host.lnm_last_error()
+
+
+@pytest.mark.parametrize("n,w,h,step,ortho,pairs", [
+    (217, 298, 77, 4.0, False, False),   # a wide view: the grid fills a tenth of its pixels
+    (160, 125, 236, 8.0, True, False),   # short marches
+    ((252, 247, 192), 326, 111, 8.0, False, False),
+    (256, 512, 512, 4.0, False, True),
+    (224, 365, 445, 4.0, False, True),
+])
+def test_plane_pairs_beside_bricks(host, n, w, h, step, ortho, pairs):
+    """Beside the caller's bricks the march asks for room for the plane pairs
+    only where its samples can repay their copy."""
+    prm = lnm.make_params(step, work_order=lnm.ORDER_Z)
+    c = camera(w, h, ortho)
+    own, given = volume(n, False), volume(n, True)
+    a, b = (host.lnm_march_workspace_bytes(C.byref(v), C.byref(c), C.byref(prm)) for v in (own, given))
+    copy = (8 * (own.nx + 2) * (own.ny + 2) * (own.nz + 1) + 255) // 256 * 256
+    assert a - b == (0 if pairs else copy)
