@@ -182,6 +182,10 @@ LNM_API lnm_status lnm_make_bricks(lnm_ctx ctx, const lnm_volume* vol, float* br
  * the same map from the bricks); 0 on invalid arguments. */
 LNM_API size_t lnm_march_workspace_bytes(const lnm_volume* vol, const lnm_camera* cam,
                                          const lnm_march_params* prm);
+/* The smallest workspace that the march accepts (without the optional copy),
+ * for callers that admit marches by memory; 0 on invalid arguments. */
+LNM_API size_t lnm_march_least_workspace_bytes(const lnm_volume* vol, const lnm_camera* cam,
+                                               const lnm_march_params* prm);
 
 /* Guiding map G[H][W][3] = (L~_scattering, T, D) per pixel: Algorithm 1 with
  * the three surrogate lights of Eq. approx (Section 4.2).  L~ = sum_n A_n L_n

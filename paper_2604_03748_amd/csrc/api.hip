@@ -665,6 +665,15 @@ size_t lnm_march_workspace_bytes(const lnm_volume* vol, const lnm_camera* cam, c
   return march_scratch_bytes(m, march_capacity(m), c.W, c.H);
 }
 
+size_t lnm_march_least_workspace_bytes(const lnm_volume* vol, const lnm_camera* cam, const lnm_march_params* prm) {
+  MarchDev m;
+  CamDev c;
+  if (march_setup(vol, cam, prm, &m, &c)) return 0;
+  const int K = march_capacity(m);
+  const size_t full = march_scratch_bytes(m, K, c.W, c.H);
+  return std::min(full, fit_march(&m, K, c.W, c.H, 0));
+}
+
 lnm_status lnm_march(lnm_ctx ctx, const lnm_volume* vol, const lnm_camera* cam, const lnm_march_params* prm,
                      float* guide, void* workspace, size_t ws_bytes, void* stream) {
   if (!ctx) return fail(LNM_ERR_ARG, "ctx is NULL");

@@ -24,7 +24,7 @@ ORDER_AUTO, ORDER_BANDS, ORDER_Z, ORDER_CELLS = 0, 1, 2, 3
 
 EXPORTS = [
     "lnm_abi_struct_size", "lnm_version", "lnm_ctx_create", "lnm_ctx_destroy", "lnm_last_error",
-    "lnm_march_workspace_bytes", "lnm_march", "lnm_march_batch_workspace_bytes", "lnm_march_batch",
+    "lnm_march_workspace_bytes", "lnm_march_least_workspace_bytes", "lnm_march", "lnm_march_batch_workspace_bytes", "lnm_march_batch",
     "lnm_reference_lightmaps", "lnm_net_param_count",
     "lnm_net_device_bytes", "lnm_net_create", "lnm_net_destroy", "lnm_workspace_bytes", "lnm_infer", "lnm_frame",
     "lnm_composite", "lnm_profile_enable", "lnm_profile_read", "lnm_trainer_state_bytes", "lnm_frame_workspace_bytes",
@@ -102,8 +102,9 @@ def lib():
         L.lnm_ctx_create.restype = i32
         L.lnm_ctx_create.argtypes = [i32, C.POINTER(vp)]
         L.lnm_ctx_destroy.argtypes = [vp]
-        L.lnm_march_workspace_bytes.restype = sz
-        L.lnm_march_workspace_bytes.argtypes = [C.POINTER(Volume), C.POINTER(Camera), C.POINTER(MarchParams)]
+        for f in (L.lnm_march_workspace_bytes, L.lnm_march_least_workspace_bytes):
+            f.restype = sz
+            f.argtypes = [C.POINTER(Volume), C.POINTER(Camera), C.POINTER(MarchParams)]
         L.lnm_frame_workspace_bytes.restype = sz
         L.lnm_frame_workspace_bytes.argtypes = [vp, C.POINTER(Volume), C.POINTER(Camera), C.POINTER(MarchParams)]
         L.lnm_march.restype = i32
@@ -310,10 +311,13 @@ class Context:
                                     _stream(stream)))
         return out
 
-    def march_workspace_bytes(self, density, sigma_scale, cam, params: MarchParams, bricks=None) -> int:
+    def march_workspace_bytes(self, density, sigma_scale, cam, params: MarchParams, bricks=None,
+                              least: bool = False) -> int:
+        """Workspace of a march; least: the smallest it accepts."""
         vol = make_volume(density, sigma_scale, bricks)
         c = make_camera(cam)
-        return int(lib().lnm_march_workspace_bytes(C.byref(vol), C.byref(c), C.byref(params)))
+        size = lib().lnm_march_least_workspace_bytes if least else lib().lnm_march_workspace_bytes
+        return int(size(C.byref(vol), C.byref(c), C.byref(params)))
 
     @_on_stream
     def march(self, density, sigma_scale, cam, params: MarchParams, out=None, workspace=None, stream=None,

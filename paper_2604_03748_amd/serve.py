@@ -7,7 +7,9 @@ resident grids and brick copies are charged when the scheduler starts (grids
 and then brick copies are admitted smallest first; a brick copy that does not
 fit is dropped and that instance's marches rebuild bricks in their per-batch
 scratch; an instance whose grid does not fit is not served), and each batch's images, activations and
-march scratch while it is in flight.  The scheduler admits pending requests
+march scratch while it is in flight (at least what its marches take; more,
+for the copies of large grids that make them faster, where that costs no other
+batch its place).  The scheduler admits pending requests
 in arrival order as stream slots and budget free up: requests of the same
 view resolution are grouped into a batch (held up to a stated deadline for
 more of the same size while other batches keep the device busy), each is
@@ -108,16 +110,23 @@ class Backend:
         return 4 * res * res * (3 + 6 + 4) + self.net.workspace_bytes(1, res, res)
 
     def batch_bytes(self, reqs, instances) -> int:
-        """Bytes a batch holds beyond its requests: one march scratch, reused
-        by the batch's marches one after the other on its stream."""
-        return max(self._march_bytes(instances[r.instance], r.frame) for r in reqs)
+        """Bytes a batch holds at least beyond its requests: one march scratch,
+        reused by the batch's marches one after the other on its stream."""
+        return max(self._march_bytes(instances[r.instance], r.frame, True) for r in reqs)
 
-    def _march_bytes(self, inst, frame):
+    def batch_bytes_wanted(self, reqs, instances) -> int:
+        """The same with room for the copies of large grids that make their
+        marches faster."""
+        return max(self._march_bytes(instances[r.instance], r.frame, False) for r in reqs)
+
+    def _march_bytes(self, inst, frame, least):
         prm = lnm.make_params(inst.step_voxels, seed=inst.seed, frame=frame)
         return self.ctx.march_workspace_bytes(inst.density, inst.sigma_scale, inst.camera(frame), prm,
-                                              bricks=inst.bricks)
+                                              bricks=inst.bricks, least=least)
 
-    def launch(self, slot: int, reqs, instances, keep_ids=()):
+    def launch(self, slot: int, reqs, instances, keep_ids=(), march_bytes=None):
+        """march_bytes: the march scratch granted to the batch (default: the
+        wanted one)."""
         import torch
 
         st = self.streams[slot]
@@ -128,7 +137,8 @@ class Backend:
             lm = torch.empty((B, res, res, 6), dtype=torch.float32, device="cuda")
             rgba = torch.empty((B, res, res, 4), dtype=torch.float32, device="cuda")
             ws = self.net.workspace(B, res, res)
-            mws = torch.empty(self.batch_bytes(reqs, instances), dtype=torch.uint8, device="cuda")
+            mws = torch.empty(march_bytes if march_bytes is not None else self.batch_bytes_wanted(reqs, instances),
+                              dtype=torch.uint8, device="cuda")
             insts = [instances[r.instance] for r in reqs]
             # the batch's marches in one call (ragged grids, one camera and seed each)
             self.ctx.march_batch([i.density for i in insts], [i.sigma_scale for i in insts],
@@ -254,13 +264,21 @@ class Scheduler:
                 extra = self.be.batch_bytes(batch, self.inst) if batch else 0
             if not batch:
                 return
-            used += extra
             slot = self.free_slots.pop()
+            granted = {}
+            if hasattr(self.be, "batch_bytes_wanted"):
+                # the larger march scratch where the budget left still holds a
+                # batch like this one, with the least scratch, on every free slot
+                wanted = self.be.batch_bytes_wanted(batch, self.inst)
+                if self.in_use + used + wanted + len(self.free_slots) * (used + extra) <= self.budget:
+                    extra = wanted
+                granted["march_bytes"] = extra
+            used += extra
             for r in batch:
                 r.t_admit = now
                 r.batch = self.n_batches
             try:
-                handle = self.be.launch(slot, batch, self.inst, self.keep_ids)
+                handle = self.be.launch(slot, batch, self.inst, self.keep_ids, **granted)
             except (lnm.LnmError, MemoryError, RuntimeError) as e:
                 # the batch never reached the device: release its slot and budget
                 self.free_slots.append(slot)

@@ -28,7 +28,8 @@ def host(tmp_path_factory):
     assert r.returncode == 0, r.stderr[-3000:]
     L = C.CDLL(so)
     vp, sz = C.c_void_p, C.c_size_t
-    for name in ("lnm_march_workspace_bytes", "lnm_net_device_bytes", "lnm_frame_workspace_bytes"):
+    for name in ("lnm_march_workspace_bytes", "lnm_march_least_workspace_bytes", "lnm_net_device_bytes",
+                 "lnm_frame_workspace_bytes"):
         getattr(L, name).restype = sz
     L.lnm_frame_workspace_bytes.argtypes = [vp, vp, vp, vp]
     L.lnm_frame_static.argtypes = [vp, vp, vp, vp, vp, vp, C.c_int32, vp, vp, vp, vp]
@@ -104,3 +105,22 @@ def test_plane_pairs_beside_bricks(host, n, w, h, step, ortho, pairs):
     a, b = (host.lnm_march_workspace_bytes(C.byref(v), C.byref(c), C.byref(prm)) for v in (own, given))
     copy = (8 * (own.nx + 2) * (own.ny + 2) * (own.nz + 1) + 255) // 256 * 256
     assert a - b == (0 if pairs else copy)
+
+
+@pytest.mark.parametrize("bricks", [False, True])
+@pytest.mark.parametrize("n,w,h,step,order", [
+    (256, 512, 512, 4.0, lnm.ORDER_AUTO), (192, 64, 64, 4.0, lnm.ORDER_AUTO), (16, 65, 41, 2.0, lnm.ORDER_AUTO),
+    (128, 256, 256, 4.0, lnm.ORDER_AUTO), (64, 31, 77, 3.0, lnm.ORDER_BANDS), ((9, 40, 22), 50, 50, 0.7, lnm.ORDER_Z),
+])
+def test_least_workspace_is_accepted(host, net, n, w, h, step, order, bricks):
+    """The march takes its least workspace and refuses one byte less; the
+    preferred size is no smaller."""
+    ctx, _ = net
+    host.lnm_march.argtypes = [C.c_void_p] * 4 + [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
+    prm = lnm.make_params(step, work_order=order)
+    v, c = volume(n, bricks), camera(w, h)
+    least, full = (f(C.byref(v), C.byref(c), C.byref(prm)) for f in
+                   (host.lnm_march_least_workspace_bytes, host.lnm_march_workspace_bytes))
+    assert 0 < least <= full
+    for size, want in ((least, 0), (least - 1, lnm.LNM_ERR_SHAPE), (full, 0), (full - 1, 0 if least < full else lnm.LNM_ERR_SHAPE)):
+        assert host.lnm_march(ctx, C.byref(v), C.byref(c), C.byref(prm), ANY, ANY, size, None) == want
