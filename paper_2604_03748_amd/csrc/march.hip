@@ -11,6 +11,7 @@
 // grids after a scatter of the records into z order) and the accumulation.
 // The fine-step reference kernel reads the linear grid.
 #include <cmath>
+#include <type_traits>
 
 #include "internal.h"
 #include "ray.h"
@@ -1612,8 +1613,9 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, bool
     // byte offsets in the box, modulo 2^32
     const int base4 = 4 * ((lo[2] * sz[1] + lo[1]) * sx + lo[0]);
     const char* corner = reinterpret_cast<const char*>(box);
+    const float start = acc;
     float top = 0.0f;
-    auto sample = [&](float kk) {
+    auto sample = [&](float kk, auto weighted) {
       const float gx = r.at(0, kk), gy = r.at(1, kk), gz = r.at(2, kk);
       const int at = __umul24((int)gz, 4 * sxy) + (__umul24((int)gy, 4 * sx) + (4 * (int)gx - base4));
       float v[8];
@@ -1624,7 +1626,9 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, bool
         v[2 * e + 1] = c[1];
       }
       const float fx = __builtin_amdgcn_fractf(gx), fy = __builtin_amdgcn_fractf(gy), fz = __builtin_amdgcn_fractf(gz);
-      auto lerp = [](float p, float q, float f) { return fmaf(f, q - p, p); };
+      auto lerp = [](float p, float q, float f) {
+        return decltype(weighted)::value ? lerp1(p, q, f) : fmaf(f, q - p, p);
+      };
       return lerp(lerp(lerp(v[0], v[1], fx), lerp(v[2], v[3], fx), fy),
                   lerp(lerp(v[4], v[5], fx), lerp(v[6], v[7], fx), fy), fz);
     };
@@ -1632,15 +1636,24 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, bool
     int j = max(k, k0);
     float kk = (float)j;
     for (; j < last; j += 2, kk += 2.0f) {
-      const float s0 = sample(kk), s1 = sample(kk + 1.0f);
+      const float s0 = sample(kk, std::false_type{}), s1 = sample(kk + 1.0f, std::false_type{});
       acc += s0;
       top = fmaxf(top, acc);
       acc += s1;
       top = fmaxf(top, acc);
     }
     if (j == last) {
-      acc += sample(kk);
+      acc += sample(kk, std::false_type{});
       top = fmaxf(top, acc);
+    }
+    // an infinite corner: the differences give NaN where the weighted form, one
+    // operation more per axis, gives infinity, and the march ends at the limit
+    if (__builtin_expect(acc != acc, 0)) {
+      acc = start;
+      for (j = max(k, k0); j <= last; ++j) {
+        acc += sample((float)j, std::true_type{});
+        top = fmaxf(top, acc);
+      }
     }
     k += steps;
     if (top > lim) {
