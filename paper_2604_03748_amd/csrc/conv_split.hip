@@ -293,6 +293,25 @@ __global__ __launch_bounds__(256, 2) void conv3x3_split(ConvArgs a, HeadFuse hf)
     }
     __syncthreads();
   }
+  // (a sum past fp32's range is infinite by its large terms alone; the small
+  // ones, of either sign, are then infinite too and would make it NaN)
+  float top = 0.0f;
+#pragma unroll
+  for (int mf = 0; mf < MF; ++mf)
+#pragma unroll
+    for (int nf = 0; nf < NF; ++nf) {
+      const f4 v = acc[mf][nf];
+      top = fmaxf(top, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+    }
+  if (__builtin_expect(top == INFINITY, 0)) {
+#pragma unroll
+    for (int mf = 0; mf < MF; ++mf)
+#pragma unroll
+      for (int nf = 0; nf < NF; ++nf)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (fabsf(acc[mf][nf][r]) == INFINITY) cor[mf][nf][r] = 0.0f;
+  }
 #pragma unroll
   for (int mf = 0; mf < MF; ++mf)
 #pragma unroll
