@@ -322,8 +322,8 @@ hipError_t launch_rows(const ConvArgs& a, hipStream_t s) {
   auto wgs = [&](int th) {
     return (long)((a.W + kTW - 1) / kTW) * ((a.H + th - 1) / th) * a.B * a.n_tiles * a.splits;
   };
-  if (wgs(16) >= 512) return launch_th<16, MODE, 16>(a, s);
-  return a.th == 4 && wgs(8) < 512 ? launch_th<16, MODE, 4>(a, s) : launch_th<16, MODE, 8>(a, s);
+  if (wgs(16) >= 512 && rows_fit(a.H, 16)) return launch_th<16, MODE, 16>(a, s);
+  return a.th == 4 && (wgs(8) < 512 || !rows_fit(a.H, 8)) ? launch_th<16, MODE, 4>(a, s) : launch_th<16, MODE, 8>(a, s);
 }
 
 }  // namespace

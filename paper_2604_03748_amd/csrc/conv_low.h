@@ -528,22 +528,23 @@ hipError_t launch_layer(const ConvArgs& a, hipStream_t s, const HeadFuse* head) 
   };
   if (a.seq > 1) {
     if constexpr (MODE == G_PLAIN || MODE == G_CONCAT_UP) {
-      if (wgs(16, 2) >= 512) return launch_tile<T, MODE, 4, 2, true>(a, s, head);
+      if (wgs(16, 2) >= 512 && rows_fit(a.H, 16)) return launch_tile<T, MODE, 4, 2, true>(a, s, head);
     }
     return launch_tile<T, MODE, 2, 2, true>(a, s, head);
   }
   const int nf = a.co % 64 == 0 ? 4 : a.co % 48 == 0 ? 3 : a.co > 32 ? 4 : 2;
   if (a.splits == 1) {
     if constexpr (MODE == G_PLAIN || MODE == G_CONCAT_UP) {
-      if (!head && wgs(16, nf) >= 512) {
+      if (!head && wgs(16, nf) >= 512 && rows_fit(a.H, 16)) {
         if (nf == 4) return launch_tile<T, MODE, 4, 4, false>(a, s, head);
         if (nf == 3) return launch_tile<T, MODE, 4, 3, false>(a, s, head);
         return launch_tile<T, MODE, 4, 2, false>(a, s, head);
       }
     }
-    if (nf == 3 && (head || wgs(8, nf) >= 512)) return launch_tile<T, MODE, 2, 3, false>(a, s, head);
-    if (nf == 4 && wgs(8, nf) >= 512) return launch_tile<T, MODE, 2, 4, false>(a, s, head);
-    if (wgs(8, 2) >= 512) return launch_tile<T, MODE, 2, 2, false>(a, s, head);
+    const bool fit = rows_fit(a.H, 8);
+    if (nf == 3 && (head || (fit && wgs(8, nf) >= 512))) return launch_tile<T, MODE, 2, 3, false>(a, s, head);
+    if (nf == 4 && fit && wgs(8, nf) >= 512) return launch_tile<T, MODE, 2, 4, false>(a, s, head);
+    if (fit && wgs(8, 2) >= 512) return launch_tile<T, MODE, 2, 2, false>(a, s, head);
   }
   return a.th == 4 ? launch_tile<T, MODE, 1, 2, false>(a, s, head) : launch_tile<T, MODE, 2, 2, false>(a, s, head);
 }

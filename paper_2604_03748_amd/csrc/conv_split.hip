@@ -468,8 +468,8 @@ int tile_rows(const ConvArgs& a, int tallest) {
   auto wgs = [&](int th) {
     return (long)((a.W + kTW - 1) / kTW) * ((a.H + th - 1) / th) * a.B * a.n_tiles * a.splits;
   };
-  if (tallest >= 4 && wgs(16) >= 512) return 4;
-  return wgs(8) >= 512 ? 2 : 1;
+  if (tallest >= 4 && wgs(16) >= 512 && rows_fit(a.H, 16)) return 4;
+  return wgs(8) >= 512 && rows_fit(a.H, 8) ? 2 : 1;
 }
 
 template <int MODE>

@@ -192,6 +192,16 @@ int conv_splits(long wgs, int nchunks, int target);
 struct LayerTiling {
   int th, splits, seq;
 };
+// Whether tiles of th rows pad an image of h rows by at most a quarter more
+// than tiles of half the height.  Batches of low images have the workgroups for
+// tall tiles without the rows: with tiles by their number alone, 36 images of
+// 32^2 through a 6-level base-32 network (1 to 4 rows in the deep levels) took
+// 511 us in fp8, 633 in bf16 and 2508 in fp32, now 294, 348 and 1081; 24 x 80 x
+// 160, 4 levels, base 48, bf16 (10 and 20 rows): 489 -> 471.
+inline bool rows_fit(int h, int th) {
+  auto padded = [&](int t) { return (h + t - 1) / t * t; };
+  return 4 * padded(th) <= 5 * padded(th / 2);
+}
 LayerTiling conv_layer_tiling(const lnm_net_s* net, int i, int B, int h, int w);
 struct HeadFuse;
 // head: the layer's epilogue also applies the 1x1 head (plain-input layers

@@ -204,7 +204,7 @@ LayerTiling conv_layer_tiling(const lnm_net_s* net, int i, int B, int h, int w) 
     const int s4 = conv_splits(wgs(4), nch, d.prec == LNM_FP32 && nch >= 16 ? 512 : target);
     if (s4 < s8 || wgs(8) <= 256 || fp8) t = {4, s4, 1};
   }
-  if (t.splits > 1 && d.prec != LNM_FP32 && B * wgs(8) >= 512) t = {8, 1, t.splits};
+  if (t.splits > 1 && d.prec != LNM_FP32 && B * wgs(8) >= 512 && rows_fit(h, 8)) t = {8, 1, t.splits};
   return t;
 }
 
