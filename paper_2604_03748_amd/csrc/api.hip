@@ -126,7 +126,7 @@ static lnm_status march_setup(const lnm_volume* vol, const lnm_camera* cam, cons
   if (m->zorder < 0)
     return fail(LNM_ERR_UNSUPPORTED, "params.work_order: a z cell's two grid planes do not fit in LDS");
   m->zorder2 = m->zorder;
-  m->zorder = march_order_short(prm->work_order, m->zorder, m->h);
+  m->zorder = march_order_short(prm->work_order, m->zorder, *m, *c);
   m->brick = vol->bricks;  // NULL: launch_march builds them in its scratch
   m->nbx = m->nby = m->nbz = 0;
   m->pair = nullptr;

@@ -110,8 +110,8 @@ int march_capacity(const MarchDev& m);
 // fit in LDS, else bands; -1 when LNM_ORDER_CELLS does not fit.
 constexpr int kOrderBands = 0, kOrderLayers = 1, kOrderCells = 2;
 int march_order(int work_order, int light_set, int nx, int ny, int nz);
-// AUTO's z cells become bands when the light marches are short (world step h).
-int march_order_short(int work_order, int order, float h);
+// AUTO's z cells become bands when the light marches are short.
+int march_order_short(int work_order, int order, const MarchDev& m, const CamDev& c);
 // Whether a march should read plane pairs (and m.pair_hits), and their bytes.
 constexpr int kPairsNone = 0, kPairsAlways = 1, kPairsAsked = 2;
 int march_pairs(MarchDev* m, const CamDev& c);

@@ -124,3 +124,19 @@ def test_least_workspace_is_accepted(host, net, n, w, h, step, order, bricks):
     assert 0 < least <= full
     for size, want in ((least, 0), (least - 1, lnm.LNM_ERR_SHAPE), (full, 0), (full - 1, 0 if least < full else lnm.LNM_ERR_SHAPE)):
         assert host.lnm_march(ctx, C.byref(v), C.byref(c), C.byref(prm), ANY, ANY, size, None) == want
+
+
+@pytest.mark.parametrize("n,w,h,step,cells", [
+    (32, 64, 64, 2.0, False),                # 16 steps, a small view
+    ((24, 48, 192), 348, 1080, 10.0, True),  # 19 steps, a large one
+    (64, 874, 693, 3.5, True),               # 18 steps
+    (128, 512, 512, 10.0, False),            # 13 steps
+    (128, 256, 256, 4.0, True),              # 32 steps
+])
+def test_order_of_short_marches(host, n, w, h, step, cells):
+    """The automatic order of short light marches, by the workspace it asks for."""
+    v, c = volume(n, False), camera(w, h)
+    size = {o: host.lnm_march_workspace_bytes(C.byref(v), C.byref(c), C.byref(lnm.make_params(step, work_order=o)))
+            for o in (lnm.ORDER_AUTO, lnm.ORDER_BANDS, lnm.ORDER_CELLS)}
+    assert size[lnm.ORDER_BANDS] != size[lnm.ORDER_CELLS]
+    assert size[lnm.ORDER_AUTO] == size[lnm.ORDER_CELLS if cells else lnm.ORDER_BANDS]
