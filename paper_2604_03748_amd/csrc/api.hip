@@ -440,7 +440,6 @@ lnm_status run_unet(lnm_ctx_s* ctx, const lnm_net_s* net, int B, int H, int W, c
   hf.lm = lm;
   if (comp) hf.comp = *comp;
   const bool last_e4m3 = net->layers[n_conv - 1].out_es == 1;  // features the head reads
-  hf.in_scale = last_e4m3 ? net->act_scale[n_conv - 1] : 1.0f;
   const LayerDesc& ld = net->layers[n_conv - 1];
   const LayerTiling lt = conv_layer_tiling(net, n_conv - 1, B, H, W);
   const bool fused = fuse_head && lm && !logits && ld.co <= (ld.prec == LNM_BF16 ? 48 : kBN) && lt.splits == 1 &&

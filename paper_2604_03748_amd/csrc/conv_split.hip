@@ -461,8 +461,8 @@ hipError_t launch_mf(const ConvArgs& a, hipStream_t s, const HeadFuse* head) {
 // each (all that 16-row tiles' LDS allows).  Taller tiles read less LDS per
 // product (a 4-row tile's reads take longer than its products) and split
 // the weights for more pixels: 8 x 256^2 on the 4-level base-32 network took
-// 1336 us with the 4-row tiles that one image takes in the deep levels, 1053
-// with these.  For one image 512 is the best as well: a 256^2 frame takes 294
+// 1.27 times as long with the 4-row tiles that one image takes in the deep
+// levels.  For one image 512 is the best as well: a 256^2 frame takes 294
 // us, 300 with 8-row tiles from 256 workgroups on and 304 from 1024 on.
 int tile_rows(const ConvArgs& a, int tallest) {
   auto wgs = [&](int th) {

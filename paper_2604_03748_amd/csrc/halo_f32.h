@@ -25,9 +25,7 @@ template <int MODE>
 __device__ __forceinline__ Halo<MODE> halo_load(const ConvArgs& a, int b, int y, int x, int c) {
   const float* s0 = static_cast<const float*>(a.src0);
   Halo<MODE> h;
-  if constexpr (MODE == G_FIRST) {
-    h.v[0] = f4{0.f, 0.f, 0.f, 0.f};
-  } else if constexpr (MODE == G_GUIDE) {
+  if constexpr (MODE == G_GUIDE) {
     const float* g = s0 + ((size_t)(b * a.H + y) * a.W + x) * 3;
     h.v[0] = f4{g[0], g[1], g[2], 0.0f};
   } else if constexpr (MODE == G_PLAIN) {

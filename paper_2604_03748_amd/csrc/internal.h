@@ -253,14 +253,14 @@ struct CompositeBatchArgs {
 };
 hipError_t launch_composite_batch(const CompositeBatchArgs& a, hipStream_t s);
 
-// The 1x1 head (+ sigmoid, + optional shading) applied in the last fp32 conv
-// layer's epilogue: that layer's workgroup holds all its channels.
+// The 1x1 head (+ sigmoid, + optional shading) applied in the last conv layer's
+// epilogue (fp32 layers up to 32 channels, bf16 ones, the last of fp8 networks
+// too, up to 48): that layer's workgroup holds all its channels.
 struct HeadFuse {
   const float* w;      // [6][C] head weights (C = the layer's output channels)
   const float* b;      // [6]
   float* lm;           // [P][6] lightmaps
   CompositeArgs comp;  // comp.rgba == nullptr: no shading
-  float in_scale;      // e4m3 layers: the scale of the layer's stored activations
 };
 
 // ---------------------------------------------------------------- channel adapters
@@ -393,8 +393,8 @@ struct Plan {
 };
 Plan plan_workspace(const lnm_net_s* net, int B, int H, int W);
 // comp (batch 1): shade each pixel in the head launch as well.  fuse_head:
-// an fp32 network may apply the head in its last conv layer's epilogue (that
-// layer's output is then not stored; callers that read it pass false).
+// the head may run in the last conv layer's epilogue (see HeadFuse; that layer's
+// output is then not stored; callers that read it pass false).
 // split: an fp32 network's products as bf16 splits (inference); training's
 // forward pass and the calibration keep the fp32 instruction's sums, which
 // decide ReLU masks and fp8 scales, as they were
@@ -433,7 +433,7 @@ struct WgradTiling {
 };
 WgradTiling wgrad_tiling(int co, int ci, int B, int h, int w);
 // weight and bias gradients (the sums and their reduction)
-hipError_t launch_wgrad3x3(int mode, const WgradArgs& a, int* n_partials, hipStream_t s);
+hipError_t launch_wgrad3x3(int mode, const WgradArgs& a, hipStream_t s);
 hipError_t launch_loss(const float* y, const float* t, float* dz, float* partial, long n, float* loss,
                        hipStream_t s);
 // partial: kHeadBwdBlocks (6 C + 6) floats

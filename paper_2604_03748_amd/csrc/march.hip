@@ -1062,8 +1062,10 @@ __global__ __launch_bounds__(256) void zsort_records(MarchBuf buf) {
 // global atomic and writes its entries there on a second pass.  Every write
 // is bounded by its cell's range.  From kSortManyPixels on the reservations of
 // all blocks queue for the cells' counters, and blocks of 128 pixels make half
-// as many (a 512^2 frame 310 -> 304 us, 304 with 256 pixels; at 256^2 64 are
-// the best: 8.7 us against 8.9 and 13.0 with 128 and 256).
+// as many: marches of 64^3 to 128^3 grids take 0.94 to 0.97 of the time from 512 x
+// 384 to 1024^2, 0.97 to 1.00 at 320^2 and 384^2, 1.005 to 1.015 at 256^2.  (With
+// 256 pixels a 512^2 frame takes what it takes with 128, the sort at 256^2 13.0
+// us against 8.9 and, with 64, 8.7.)
 constexpr int kSortManyPixels = 131072;
 template <int PX>
 __global__ __launch_bounds__(256) void zsort_cells(MarchBuf buf) {
@@ -1464,7 +1466,7 @@ __device__ __forceinline__ float ray_value(const MarchDev& m, const GridRay& r, 
 }
 
 // Voxels of a reference march's LDS box (8 KB: LDS then admits five
-// wavefronts per SIMD, as many as the registers do).
+// wavefronts per SIMD, the registers four).
 constexpr int kRefBox = 2048;
 
 // largest value of the wavefront, in a scalar (DPP: within rows of 16 lanes,
@@ -1705,7 +1707,7 @@ __device__ __forceinline__ float reference_transmittance(const MarchDev& m, bool
 // a thousand times one beside it, so the wavefronts are workgroups of their
 // own (four to a workgroup left CUs with one running wavefront: 18.4 ms), and
 // each tile row starts three columns further along, which spreads the
-// volume's columns over the XCDs.  128^3, 256^2, half-voxel steps: 2.9 to 3.3
+// volume's columns over the XCDs.  128^3, 256^2, half-voxel steps: 2.8 to 3.4
 // ms (by scene), vector instructions 86% busy, most of them the interior
 // samples' 33 each; 5.8 to 7.1 ms with every corner gathered from
 // memory and whole marches from the border in border steps, 114 to 163 ms with

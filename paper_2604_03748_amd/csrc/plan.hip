@@ -24,8 +24,13 @@ size_t bricks_bytes(int nx, int ny, int nz) {
 }
 
 // Bricked grids above this size (the eight XCDs' L2s together) take the z
-// order: measured at 256^3 / 1024^2, march 4.30 -> 2.73 ms; at 128^3 /
-// 256^2 the scatter's launch costs more than the order saves.
+// order: at 256^3 / 1024^2 the march took 4.30 ms in bands, 2.73 in z order on
+// bricks and takes 1.7 on plane pairs.  Smaller grids whose planes do not fit
+// in LDS stay in bands, which took 0.68 to 1.5 of the z order's time with pairs
+// (7 to 30 MB of bricks, planes of 160 x 160 to 200 x 200, 64 to 700 pixels a
+// side; 2 to 4 times on planes of 700 columns); so do the left/right lights,
+// whose marches leave their z cell: 0.61 to 1.2 below the border (112^3 at 367 x
+// 662 2.1), 0.62 to 1.4 above it.
 constexpr size_t kZOrderBytes = (size_t)32 << 20;
 static int tiles_per_band(int W, int H) { return (((W + kTile - 1) / kTile) * ((H + kTile - 1) / kTile) + 7) / 8; }
 
@@ -180,13 +185,15 @@ int conv_splits(long wgs, int nchunks, int target) {
 // of th x 16 pixels x 32 output channels); the 3-channel input layer is
 // never split.  The split grows until the layer has 256 workgroups (fp32) or
 // 512 (bf16, fp8), the targets measured fastest per precision with the
-// split-K reductions counted.  fp32 and bf16 layers take 4-row tiles where
-// that needs a smaller split than 8-row tiles (the deep levels: twice the
-// workgroups without partial sums to write, read and reduce) or where 8-row
-// tiles leave one workgroup per CU (nothing else on the CU hides a
-// workgroup's chunk-boundary stalls): 5 us per fp32 frame, 9 us per bf16
-// frame.  fp8 layers, whose LDS footprint lets five 4-row workgroups share
-// a CU, take 4-row tiles throughout: 19 us per frame.
+// split-K reductions counted (the fp32 networks of nine small inputs with 512
+// instead: 0.98 to 1.06 of the time, with 128 0.99 to 1.02).  The height given
+// here is that of the fp32 instruction's kernel, which training and calibration
+// run, and, for layers too small for more, of the bf16 and fp8 kernel; the split
+// fp32 kernel takes its own.  4-row tiles where they need a smaller split than
+// 8-row tiles (the deep levels: twice the workgroups without partial sums to
+// write, read and reduce) or where 8-row tiles leave one workgroup per CU
+// (nothing else on the CU hides a workgroup's chunk-boundary stalls); fp8
+// layers, whose LDS footprint lets five 4-row workgroups share a CU, throughout.
 //
 // The split and the tile height follow the workgroup count of one image, so
 // an image's sums (whose order the split sets) are the same alone and in any
@@ -204,6 +211,7 @@ LayerTiling conv_layer_tiling(const lnm_net_s* net, int i, int B, int h, int w) 
   const bool fp8 = d.prec == LNM_FP8_E4M3;
   if (s8 > 1 || wgs(8) <= 256 || fp8) {
     // the longest fp32 layers (16+ chunks) split on to two workgroups per CU
+    // (a 256^2 frame 308 us against 318, other small inputs up to 6%)
     const int s4 = conv_splits(wgs(4), nch, d.prec == LNM_FP32 && nch >= 16 ? 512 : target);
     if (s4 < s8 || wgs(8) <= 256 || fp8) t = {4, s4, 1};
   }

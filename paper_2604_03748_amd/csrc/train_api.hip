@@ -270,10 +270,9 @@ lnm_status grad_impl(lnm_ctx ctx, lnm_trainer tr, int B, int H, int W, const flo
     wa.bias_partial = bpart;
     wa.grad_w = tr->g + tr->flat_w[i];
     wa.grad_b = tr->g + tr->flat_b[i];
-    int n_part = 0;
     {
       ProfScope ps(ctx, LNM_K_CONV, s);
-      LNM_HIP_CHECK(launch_wgrad3x3(c.mode, wa, &n_part, s));
+      LNM_HIP_CHECK(launch_wgrad3x3(c.mode, wa, s));
     }
     if (i == 0) break;
     // gradient with respect to the layer's input: the convolution with the

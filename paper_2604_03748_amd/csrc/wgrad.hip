@@ -469,13 +469,12 @@ hipError_t launch_wgrad_mode(const WgradArgs& a, const WgradTiling& t, hipStream
 
 }  // namespace
 
-hipError_t launch_wgrad3x3(int mode, const WgradArgs& a0, int* n_partials, hipStream_t s) {
+hipError_t launch_wgrad3x3(int mode, const WgradArgs& a0, hipStream_t s) {
   WgradArgs a = a0;
   const WgradTiling t = wgrad_tiling(a.co, a.ci, a.x.B, a.x.H, a.x.W);
   a.co_pad = t.co_pad;
   a.ci_pad = t.ci_pad;
   a.tiles_per_group = t.tiles_per_group;
-  *n_partials = t.groups;
   hipError_t e;
   switch (mode) {
     case G_GUIDE: e = launch_wgrad_mode<G_GUIDE>(a, t, s); break;

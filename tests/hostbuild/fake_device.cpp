@@ -88,19 +88,10 @@ hipError_t launch_adapters_train(int, const AdapterTrainArgs&, const float*, flo
 hipError_t launch_fill_zero(float*, long, hipStream_t) LAUNCH()
 hipError_t launch_shadow_map_sphere(int, float, float, float, float, float, float*, hipStream_t) LAUNCH()
 hipError_t launch_composite_shadowed(const ShadowArgs&, hipStream_t) LAUNCH()
-hipError_t launch_wgrad3x3(int, const WgradArgs&, int* n_partials, hipStream_t) {
-  *n_partials = 4;
-  ++g_launches;
-  return tick();
-}
-hipError_t launch_wgrad_reduce(const float*, int, int, int, int, int, float*, hipStream_t) LAUNCH()
+hipError_t launch_wgrad3x3(int, const WgradArgs&, hipStream_t) LAUNCH()
 hipError_t launch_loss(const float*, const float*, float*, float*, long, float*, hipStream_t) LAUNCH()
-hipError_t launch_colsum(const float*, long, int, float*, float*, hipStream_t) LAUNCH()
-hipError_t launch_relu_mask(float*, const float*, long, hipStream_t) LAUNCH()
 hipError_t launch_head_bwd(const float*, const float*, const float*, long, int, float*, float*, float*, float*,
                            hipStream_t) LAUNCH()
-hipError_t launch_route_concat(const float*, int, int, int, int, int, float*, float*, hipStream_t) LAUNCH()
-hipError_t launch_route_pool(const float*, const float*, int, int, int, int, float*, hipStream_t) LAUNCH()
 hipError_t launch_adam(float*, const float*, float*, float*, long, float, float, float, float, int, hipStream_t) LAUNCH()
 hipError_t launch_pack_f32(const float*, const float*, const LayerDesc&, int, char*, size_t, size_t, hipStream_t)
     LAUNCH()
