@@ -58,7 +58,7 @@ typedef enum { LNM_LIGHTS_TOP_BOTTOM = 0, LNM_LIGHTS_LEFT_RIGHT = 1 } lnm_light_
  * (nx + 2)(ny + 2) <= 19968 and nz < 256; LNM_ERR_UNSUPPORTED otherwise);
  * LNM_ORDER_AUTO: z order when the bricked grid exceeds 32 MiB, else cells
  * for the top/bottom lights when they fit and the light marches are not short
- * (the grid's longest axis takes more than 20 steps, or more than 13 in a view
+ * (the grid's longest axis takes more than 20 steps, or more than 16 in a view
  * of many samples), else bands. */
 typedef enum { LNM_ORDER_AUTO = 0, LNM_ORDER_BANDS = 1, LNM_ORDER_Z = 2, LNM_ORDER_CELLS = 3 } lnm_work_order;
 

@@ -267,10 +267,13 @@ class Scheduler:
             slot = self.free_slots.pop()
             granted = {}
             if hasattr(self.be, "batch_bytes_wanted"):
-                # the larger march scratch where the budget left still holds a
-                # batch like this one, with the least scratch, on every free slot
+                # the larger march scratch where the budget left still holds, on
+                # the free slots, the batches that wait, each like this one with
+                # the least scratch
                 wanted = self.be.batch_bytes_wanted(batch, self.inst)
-                if self.in_use + used + wanted + len(self.free_slots) * (used + extra) <= self.budget:
+                sizes = collections.Counter(self.inst[r.instance].res for r in pending)
+                waiting = sum(-(-n // self.max_batch) for n in sizes.values())
+                if self.in_use + used + wanted + min(waiting, len(self.free_slots)) * (used + extra) <= self.budget:
                     extra = wanted
                 granted["march_bytes"] = extra
             used += extra

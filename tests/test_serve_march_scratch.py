@@ -68,6 +68,15 @@ def test_the_larger_scratch_takes_no_batch_its_place():
     assert be.granted.count(WANTED) >= 1 and LEAST in be.granted
 
 
+def test_a_lone_batch_gets_the_larger_scratch():
+    # nothing waits, so the free slots keep no room
+    clock = FakeClock()
+    be = ScratchBackend(clock, 3)
+    sch = Scheduler(be, {0: Inst(10)}, WANTED + 200, max_batch=1, clock=clock)
+    st = sch.run([Request(k, 0, k, 0.01 * k) for k in range(4)])
+    assert st["requests"] == 4 and be.granted == [WANTED] * 4
+
+
 def test_ample_budget_grants_the_larger_scratch():
     st, be = _run(10**6, 3)
     assert st["requests"] == 12 and set(be.granted) == {WANTED}
