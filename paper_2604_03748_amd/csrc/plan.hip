@@ -127,9 +127,9 @@ int march_pairs(MarchDev* m, const CamDev& c) {
 // Light marches of few steps across the grid do not pay for staging planes in
 // LDS and sorting the records.  220 marches of 5 to 20 steps over 16^3 to 128^3
 // and oblong grids, views of 32 to 1024 pixels a side: up to 16 steps the bands
-// took 0.73 to 1.10 of the cells' time (one march 1.19; the mean 0.90), from
-// 16 to 20 0.80 to 1.09 where the view takes under 50000 primary samples in the
-// grid and up to 1.28 above.  (24 x 48 x 192, 19 steps, 348 x 1080: 256 us in
+// took 0.73 to 1.10 of the cells' time (one march 1.19; the mean 0.91), from
+// 16 to 20 0.84 to 1.09 where the view takes under 50000 primary samples in the
+// grid and 0.89 to 1.28 above.  (24 x 48 x 192, 19 steps, 348 x 1080: 256 us in
 // band order, 210 in cells.)
 int march_order_short(int work_order, int order, const MarchDev& m, const CamDev& c) {
   if (work_order != LNM_ORDER_AUTO || order != kOrderCells || 20.0f * m.h < 1.0f) return order;
